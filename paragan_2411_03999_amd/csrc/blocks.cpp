@@ -127,6 +127,8 @@ struct GWsF {
   void* sn;
   void* bn;
   float* skip;
+  void* cp;          // partials of split convs
+  size_t cp_bytes;
 };
 struct GWsB {
   void *wd1, *wd2, *wdsc;
@@ -138,6 +140,8 @@ struct GWsB {
   void* dh1;
   float *dg1, *db1, *dg2, *db2, *part, *lin;
   void* bnb;
+  void* cp;          // partials of split convs
+  size_t cp_bytes;
 };
 
 static size_t g_sn_ws(const GBlock& g) {
@@ -152,6 +156,10 @@ static GWsF g_carve_f(const GBlock& g, Arena& a) {
   w.sn = a.bytes(g_sn_ws(g));
   w.bn = a.bytes(std::max(bn_stats_ws_bytes(M1, g.cin), bn_stats_ws_bytes(M2, g.cout)));
   w.skip = a.f32((size_t)M1 * g.Cop);
+  w.cp_bytes = g.f32 ? 0 : std::max({conv_split_ws(G_SUB, g.B, g.H, g.W, 2, g.Cip, g.Cop),
+                                     conv_split_ws(G_DIRECT, g.B, g.H, g.W, 1, g.Cip, g.Cop),
+                                     conv_split_ws(G_DIRECT, g.B, 2 * g.H, 2 * g.W, 3, g.Cop, g.Cop)});
+  w.cp = a.bytes(w.cp_bytes);
   return w;
 }
 
@@ -182,6 +190,10 @@ static GWsB g_carve_b(const GBlock& g, Arena& a, int n_cu) {
   w.part = a.f32((size_t)kSnbParts * kSnGroupMax);
   w.lin = (float*)a.bytes(cbn_linear_bwd_ws_bytes(g.B, g.dc));
   w.bnb = a.bytes(std::max(bn_bwd_ws_bytes(g.B, 4 * g.H * g.W, g.cout), bn_bwd_ws_bytes(g.B, g.H * g.W, g.cin)));
+  w.cp_bytes = g.f32 ? 0 : std::max({conv_split_ws(G_S2, g.B, g.H, g.W, 2, g.Cop, g.Cip),
+                                     conv_split_ws(G_DIRECT, g.B, 2 * g.H, 2 * g.W, 3, g.Cop, g.Cop),
+                                     conv_split_ws(G_S2, g.B, g.H, g.W, 4, g.Cop, g.Cip)});
+  w.cp = a.bytes(w.cp_bytes);
   return w;
 }
 
@@ -249,9 +261,9 @@ void GBlock::fwd(const Exec& ex, const Params& P, const void* x, const float* co
   if (!f32) {
     // bf16: the four sub-pixel 2x2 convs over a1 itself
     in.gather = G_SUB;
-    conv_fwd(ex.st, f32, in, H, W, 2, wp1, Cop, o);
+    conv_fwd(ex.st, f32, in, H, W, 2, wp1, Cop, o, w.cp, w.cp_bytes);
   } else {
-    conv_fwd(ex.st, f32, in, 2 * H, 2 * W, 3, wp1, Cop, o);
+    conv_fwd(ex.st, f32, in, 2 * H, 2 * W, 3, wp1, Cop, o, w.cp, w.cp_bytes);
   }
   // cBN2
   bn_stats(ex.st, f32, h1, M2, cout, Cop, bn_eps, mean2, rstd2, w.bn);
@@ -262,7 +274,7 @@ void GBlock::fwd(const Exec& ex, const Params& P, const void* x, const float* co
   si.x = x; si.B = B; si.Hx = H; si.Wx = W; si.C = Cip;
   ConvOut so;
   so.y = w.skip; so.y_f32 = 1; so.yC = Cop; so.n_real = cout; so.bias = P.w("sc.b"); so.acc_div = sn[6].sigma;
-  conv_fwd(ex.st, f32, si, H, W, 1, wpsc, Cop, so);
+  conv_fwd(ex.st, f32, si, H, W, 1, wpsc, Cop, so, w.cp, w.cp_bytes);
   // y = conv3x3(a2) + b2 + up2(skip), a2 = relu(cbn2(h1))
   bn_apply(ex.st, f32, h1, M2, 4 * H * W, cout, Cop, mean2, scale2, bias2, Cop, true, a2);
   ConvIn i2;
@@ -270,7 +282,7 @@ void GBlock::fwd(const Exec& ex, const Params& P, const void* x, const float* co
   ConvOut o2;
   o2.y = y; o2.y_f32 = f32; o2.yC = Cop; o2.n_real = cout; o2.bias = P.w("conv2.b"); o2.acc_div = sn[5].sigma;
   o2.res = w.skip; o2.res_f32 = 1; o2.res_mode = R_HALF; o2.resC = Cop;
-  conv_fwd(ex.st, f32, i2, 2 * H, 2 * W, 3, wp2, Cop, o2);
+  conv_fwd(ex.st, f32, i2, 2 * H, 2 * W, 3, wp2, Cop, o2, w.cp, w.cp_bytes);
 }
 
 // The weight gradients of a block backward (and their bias column sums)
@@ -331,13 +343,13 @@ void GBlock::bwd(const Exec& ex, const Params& P, const void* x, const float* co
   dsp.x = dy; dsp.B = B; dsp.Hx = H2; dsp.Wx = W2; dsp.C = Cop; dsp.gather = f32 ? G_POOL2 : G_S2;
   ConvOut dso;
   dso.y = w.dxs; dso.y_f32 = 1; dso.yC = Cip; dso.n_real = cin; dso.acc_div = sn[6].sigma;
-  conv_fwd(ex.st, f32, dsp, H, W, f32 ? 1 : 2, wdsc, Cip, dso);
+  conv_fwd(ex.st, f32, dsp, H, W, f32 ? 1 : 2, wdsc, Cip, dso, w.cp, w.cp_bytes);
   // da2 = conv2^T dy (fp32)
   ConvIn d2;
   d2.x = dy; d2.B = B; d2.Hx = H2; d2.Wx = W2; d2.C = Cop;
   ConvOut d2o;
   d2o.y = w.da2; d2o.y_f32 = 1; d2o.yC = Cop; d2o.n_real = cout; d2o.acc_div = sn[5].sigma;
-  conv_fwd(ex.st, f32, d2, H2, W2, 3, wd2, Cop, d2o);
+  conv_fwd(ex.st, f32, d2, H2, W2, 3, wd2, Cop, d2o, w.cp, w.cp_bytes);
   // cBN2 backward (through the ReLU) -> dh1
   bn_bwd(ex.st, f32, w.da2, false, h1, B, H2, W2, cout, Cop, mean2, rstd2, gain2, bias2, Cop, nullptr, w.dh1,
          w.dg2, w.db2, Cop, w.bnb);
@@ -365,9 +377,9 @@ void GBlock::bwd(const Exec& ex, const Params& P, const void* x, const float* co
   d1o.y = w.da1; d1o.y_f32 = 1; d1o.yC = Cip; d1o.n_real = cin; d1o.acc_div = sn[2].sigma;
   if (!f32) {
     d1.gather = G_S2;
-    conv_fwd(ex.st, f32, d1, H, W, 4, wd1, Cip, d1o);
+    conv_fwd(ex.st, f32, d1, H, W, 4, wd1, Cip, d1o, w.cp, w.cp_bytes);
   } else {
-    conv_fwd(ex.st, f32, d1, H2, W2, 3, wd1, Cip, d1o);
+    conv_fwd(ex.st, f32, d1, H2, W2, 3, wd1, Cip, d1o, w.cp, w.cp_bytes);
   }
   bn_bwd(ex.st, f32, w.da1, f32, x, B, H, W, cin, Cip, mean1, rstd1, gain1, bias1, Cip, w.dxs, dx, w.dg1,
          w.db1, Cip, w.bnb);
@@ -420,6 +432,8 @@ void DBlock::plan_saved(Arena& a) {
 struct DWsF {
   void* sn;
   float* skip;
+  void* cp;          // partials of split convs
+  size_t cp_bytes;
 };
 struct DWsB {
   void *wd1, *wd2, *wdsc;
@@ -431,6 +445,8 @@ struct DWsB {
   float* dxs;
   float* part;
   float* dcol;   // im2col: gradient of the 3x3 patches
+  void* cp;      // partials of split convs
+  size_t cp_bytes;
 };
 
 static DWsF d_carve_f(const DBlock& d, Arena& a) {
@@ -438,6 +454,11 @@ static DWsF d_carve_f(const DBlock& d, Arena& a) {
   const int64_t rc[3][2] = {{d.cout, 9LL * d.cin}, {d.cout, 9LL * d.cout}, {d.cout, d.cin}};
   w.sn = a.bytes(sn_group_ws(rc, d.lsc ? 3 : 2));
   w.skip = d.lsc ? a.f32((size_t)d.B * d.Ho * d.Wo * d.Cop) : nullptr;
+  w.cp_bytes = d.f32 ? 0 : std::max({conv_split_ws(G_DIRECT, d.B, d.H, d.W, d.im2col ? 1 : 3, d.Cip, d.Cop),
+                                     conv_split_ws(G_DIRECT, d.B, d.Ho, d.Wo, 1, d.Cip, d.Cop),
+                                     d.s2conv() ? conv_split_ws(G_S2, d.B, d.Ho, d.Wo, 4, d.Cop, d.Cop)
+                                                : conv_split_ws(G_DIRECT, d.B, d.H, d.W, 3, d.Cop, d.Cop)});
+  w.cp = a.bytes(w.cp_bytes);
   return w;
 }
 
@@ -463,6 +484,11 @@ static DWsB d_carve_b(const DBlock& d, Arena& a, int n_cu) {
   w.dxs = d.lsc ? a.f32((size_t)Mo * d.Cip) : nullptr;
   w.part = a.f32((size_t)kSnbParts * kSnGroupMax);
   w.dcol = d.im2col ? a.f32((size_t)M * d.Cip) : nullptr;
+  w.cp_bytes = d.f32 ? 0 : std::max({d.subdgrad() ? conv_split_ws(G_SUB, d.B, d.Ho, d.Wo, 2, d.Cop, d.Cop)
+                                                  : conv_split_ws(G_DIRECT, d.B, d.H, d.W, 3, d.Cop, d.Cop),
+                                     conv_split_ws(G_DIRECT, d.B, d.Ho, d.Wo, 1, d.Cop, d.Cip),
+                                     conv_split_ws(G_DIRECT, d.B, d.H, d.W, d.im2col ? 1 : 3, d.Cop, d.Cip)});
+  w.cp = a.bytes(w.cp_bytes);
   return w;
 }
 
@@ -529,7 +555,7 @@ void DBlock::fwd(const Exec& ex, const Params& P, const void* x, void* y) {
   i1.x = x; i1.B = B; i1.Hx = H; i1.Wx = W; i1.C = Cip; i1.relu = preact; i1.c_real = K1;
   ConvOut o1;
   o1.y = h; o1.y_f32 = f32; o1.yC = Cop; o1.n_real = cout; o1.bias = P.w("conv1.b"); o1.acc_div = sn[0].sigma;
-  conv_fwd(ex.st, f32, i1, H, W, R1, wp1, Cop, o1);
+  conv_fwd(ex.st, f32, i1, H, W, R1, wp1, Cop, o1, w.cp, w.cp_bytes);
   // skip = conv1x1([avgpool](x)) + bsc, fp32
   if (lsc) {
     ConvIn si;
@@ -540,7 +566,7 @@ void DBlock::fwd(const Exec& ex, const Params& P, const void* x, void* y) {
     }
     ConvOut so;
     so.y = w.skip; so.y_f32 = 1; so.yC = Cop; so.n_real = cout; so.bias = P.w("sc.b"); so.acc_div = sn[2].sigma;
-    conv_fwd(ex.st, f32, si, Ho, Wo, 1, wpsc, Cop, so);
+    conv_fwd(ex.st, f32, si, Ho, Wo, 1, wpsc, Cop, so, w.cp, w.cp_bytes);
   }
   // y = [avgpool](conv3x3(relu(h)) + b2) + skip; with downsampling in bf16 the
   // pool is folded into the filter: a stride-2 4x4 conv at the pooled pixels
@@ -555,9 +581,9 @@ void DBlock::fwd(const Exec& ex, const Params& P, const void* x, void* y) {
   if (s2conv()) {
     i2.gather = G_S2;
     o2.pool = 0;
-    conv_fwd(ex.st, f32, i2, Ho, Wo, 4, wp2, Cop, o2);
+    conv_fwd(ex.st, f32, i2, Ho, Wo, 4, wp2, Cop, o2, w.cp, w.cp_bytes);
   } else {
-    conv_fwd(ex.st, f32, i2, H, W, 3, wp2, Cop, o2);
+    conv_fwd(ex.st, f32, i2, H, W, 3, wp2, Cop, o2, w.cp, w.cp_bytes);
   }
 }
 
@@ -609,9 +635,9 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
   if (subdgrad()) {
     // conv2^T over up2(dy) / 4 as the four sub-pixel 2x2 convs over dy
     d2.gather = G_SUB;
-    conv_fwd(ex.st, f32, d2, Ho, Wo, 2, wd2, Cop, d2o);
+    conv_fwd(ex.st, f32, d2, Ho, Wo, 2, wd2, Cop, d2o, w.cp, w.cp_bytes);
   } else {
-    conv_fwd(ex.st, f32, d2, H, W, 3, wd2, Cop, d2o);
+    conv_fwd(ex.st, f32, d2, H, W, 3, wd2, Cop, d2o, w.cp, w.cp_bytes);
   }
   // conv1
   GradIn g1;
@@ -640,7 +666,7 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
       ds.x = dy; ds.B = B; ds.Hx = Ho; ds.Wx = Wo; ds.C = Cop;
       ConvOut dso;
       dso.y = w.dxs; dso.y_f32 = 1; dso.yC = Cip; dso.n_real = ksc + cin; dso.acc_div = sn[2].sigma;
-      conv_fwd(ex.st, f32, ds, Ho, Wo, 1, wdsc, Cip, dso);
+      conv_fwd(ex.st, f32, ds, Ho, Wo, 1, wdsc, Cip, dso, w.cp, w.cp_bytes);
     }
   }
   if (dx) {
@@ -659,7 +685,7 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
     } else {
       d1o.res = dy; d1o.res_f32 = f32; d1o.resC = Cop; d1o.res_mode = R_SAME;
     }
-    conv_fwd(ex.st, f32, d1, H, W, R1, wd1, Cip, d1o);
+    conv_fwd(ex.st, f32, d1, H, W, R1, wd1, Cip, d1o, w.cp, w.cp_bytes);
     if (im2col) im2col_grad(ex.st, w.dcol, B, H, W, (float*)dx);
   }
   if (!wgrad) return;

@@ -434,7 +434,7 @@ static std::string launch_mfma_cfg(hipStream_t s, ConvK& k, int gather, bool aff
 }
 
 void conv_fwd(hipStream_t s, bool f32, const ConvIn& in, int H, int W, int R,
-              const void* w, int Np, const ConvOut& out) {
+              const void* w, int Np, const ConvOut& out, void* part, size_t part_bytes) {
   ConvK k;
   k.a = AOp{in.x, in.B, in.Hx, in.Wx, in.C, in.gscale, in.mean, in.scale, in.shift,
             in.tab_stride, H, W, R, R / 2, (int64_t)in.B * H * W};
@@ -484,7 +484,7 @@ void conv_fwd(hipStream_t s, bool f32, const ConvIn& in, int H, int W, int R,
     ConvIn in2 = in;
     in2.gscale = k.a.gscale;
     if (conv_fwd_mfma_ok(in2, H, W, R, Np, k.o)) {
-      const std::string name = conv_fwd_mfma(s, in2, H, W, R, w, Np, k.o);
+      const std::string name = conv_fwd_mfma(s, in2, H, W, R, w, Np, k.o, part, part_bytes);
       PG_LAUNCH_CHECK();
       prof.done(name, flops, k.a.M, Np, (int64_t)R * R * in.C);
       return;

@@ -37,8 +37,39 @@ struct CfK {
   int M, Np, ksteps;
   FastDiv fdW, fdH;
   int tiles_m, tiles_n;
+  // split of K: each split takes `per` units of the K loop (ring kernel: K
+  // steps; halo kernel: chunks) and writes its raw fp32 sums at o.y + split *
+  // split_stride (see conv_split_fin); one split: per covers the whole loop
+  int splits, per;
+  int64_t split_stride;
   ConvOut o;
 };
+
+// Tile (tmi, tni), split and parity class of a block.  Unsplit: n tiles
+// fastest (the blocks of an XCD share activations); split launches, which
+// have few pixels and much weight, take m tiles fastest within an (n tile,
+// split), so the blocks that read the same weights run back to back on one
+// XCD.  The parity class of the sub-pixel gather varies fastest either way.
+struct CfBlk {
+  int tmi, tni, split, par;
+};
+template <bool SUB>
+PG_DEV CfBlk cf_block(const CfK& k, int lin) {
+  CfBlk b;
+  b.par = SUB ? (lin & 3) : 0;
+  const int bid = SUB ? (lin >> 2) : lin;
+  if (k.splits == 1) {
+    b.tmi = bid / k.tiles_n;
+    b.tni = bid - b.tmi * k.tiles_n;
+    b.split = 0;
+  } else {
+    const int t = bid / k.tiles_m;   // split * tiles_n + tni
+    b.tmi = bid - t * k.tiles_m;
+    b.split = t / k.tiles_n;
+    b.tni = t - b.split * k.tiles_n;
+  }
+  return b;
+}
 
 PG_DEV int remap_tile2(int bid, int total) {
   // Blocks are dispatched round-robin over the 8 XCDs; give each XCD a
@@ -116,7 +147,7 @@ PG_DEV void conv_step(const bf16_t* xs, const bf16_t* ws, int xbase, int wbase, 
 // barrier here.
 template <int WN, int WM, int TN, int TM, int GATHER>
 PG_DEV void conv_epilogue(const CfK& k, f32x16 (&acc)[TN][TM], bf16_t* lds, int m0, int n0, int wn, int wm,
-                          int wave, int lane, int pa, int pb) {
+                          int wave, int lane, int pa, int pb, int split) {
   constexpr int NW = WN * WM, NT = NW * 64, BN = WN * TN * 32;
   constexpr int SROW = TN * 32 + 4;            // staging floats per pixel row
   const int tid = wave * 64 + lane, lr = lane & 31, h = lane >> 5;
@@ -235,7 +266,7 @@ PG_DEV void conv_epilogue(const CfK& k, f32x16 (&acc)[TN][TM], bf16_t* lds, int 
           if (n + e >= o.n_real) v[e] = 0.f;
       }
       if (o.y_f32) {
-        float* yp = (float*)o.y + yo[t];
+        float* yp = (float*)o.y + split * k.split_stride + yo[t];
         *reinterpret_cast<float4*>(yp) = make_float4(v[0], v[1], v[2], v[3]);
         *reinterpret_cast<float4*>(yp + 4) = make_float4(v[4], v[5], v[6], v[7]);
       } else {
@@ -272,11 +303,9 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k)
   // sub-pixel gather: the parity class (a, b) of this block's output pixels
   // varies fastest, so the four classes of a tile run back to back on one
   // XCD and their interleaved output pixels meet in its L2
-  const int lin = remap_tile2(blockIdx.x, k.tiles_m * k.tiles_n * (GATHER == G_SUB ? 4 : 1));
-  const int par = GATHER == G_SUB ? (lin & 3) : 0;
-  const int bid = GATHER == G_SUB ? (lin >> 2) : lin;
-  const int tmi = bid / k.tiles_n, tni = bid - tmi * k.tiles_n;
-  const int m0 = tmi * BM, n0 = tni * BN;
+  const CfBlk blk = cf_block<GATHER == G_SUB>(k, remap_tile2(blockIdx.x, gridDim.x));
+  const int par = blk.par;
+  const int m0 = blk.tmi * BM, n0 = blk.tni * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave / WM, wm = wave % WM;
@@ -328,9 +357,14 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k)
     woff[j] = row < BN && n < k.Np ? (uint32_t)((par * k.Np + n) * R * R * C) * 2u + 16u * lchunk : kOOB;
   }
 
+  // this block's K steps: ksteps of them from ks0 (all of them unless split)
+  const int ks0 = blk.split * k.per;
+  const int ksteps = min(k.per, k.ksteps - ks0);
   // producer position (tap, channel offset, step)
-  int ld_tap = 0, ld_c0 = 0, ld_ks = 0;
-  set_tap(0);
+  const int cst = C / KS;
+  int ld_tap = ks0 / cst, ld_ks = ks0;
+  int ld_c0 = (ks0 - ld_tap * cst) * KS;
+  set_tap(ld_tap);
   auto advance = [&]() {
     ++ld_ks;
     ld_c0 += KS;
@@ -369,7 +403,6 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-  const int ksteps = k.ksteps;
   // Ring of NS stages: the loads of step s go to stage s % NS and are issued
   // NS - 1 steps ahead.  Step ks first waits until its own loads have landed
   // (those of the up to NS - 2 later steps may still fly) and this wave's
@@ -398,7 +431,7 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k)
     conv_step<TN, TM, RELU, KS>(Xs[st], Ws[st], xbase, wbase, rdo, acc);
   }
 
-  conv_epilogue<WN, WM, TN, TM, GATHER>(k, acc, lds, m0, n0, wn, wm, wave, lane, pa, pb);
+  conv_epilogue<WN, WM, TN, TM, GATHER>(k, acc, lds, m0, n0, wn, wm, wave, lane, pa, pb, blk.split);
 }
 
 // Halo variant for the 3x3, pad-1 convolution over the direct gather
@@ -448,11 +481,9 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_halo(CfK k
   __shared__ __attribute__((aligned(16))) bf16_t lds[RING > EPI ? RING : EPI];
 
   // sub-pixel gather: parity class fastest (as in k_conv_fwd)
-  const int lin = remap_tile2(blockIdx.x, k.tiles_m * k.tiles_n * (GK == G_SUB ? 4 : 1));
-  const int par = GK == G_SUB ? (lin & 3) : 0;
-  const int bid = GK == G_SUB ? (lin >> 2) : lin;
-  const int tmi = bid / k.tiles_n, tni = bid - tmi * k.tiles_n;
-  const int m0 = tmi * BM, n0 = tni * BN;
+  const CfBlk blk = cf_block<GK == G_SUB>(k, remap_tile2(blockIdx.x, gridDim.x));
+  const int par = blk.par;
+  const int m0 = blk.tmi * BM, n0 = blk.tni * BN;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = wave / WM, wm = wave % WM;
@@ -548,15 +579,17 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_halo(CfK k
   // reads weight stage (s - 1) % NSW or patch buffer (c + 1) % 2 (last read
   // in chunk c - 1) any more before they refill.
   static_assert(NSW >= 2 && NSW <= T, "the next patch is issued within a chunk");
-  const int nch = (GK == G_S2 ? 4 : 1) * (C / 32), S = T * nch;
-  issue_patch(0, 0);
+  // this block's chunks cb0 .. ce - 1 (all of them unless split), steps S0 .. S - 1
+  const int cb0 = blk.split * k.per;
+  const int ce = min(cb0 + k.per, (GK == G_S2 ? 4 : 1) * (C / 32)), S0 = T * cb0, S = T * ce;
+  issue_patch(cb0 & 1, cb0);
 #pragma unroll
   for (int st = 0; st < NSW - 1; ++st)
-    if (st < S) issue_w(st, st);
-  int sb = 0;   // ring stage of the chunk's first tap, (T c) % NSW
-  for (int c = 0; c < nch; ++c) {
+    if (S0 + st < S) issue_w(st, S0 + st);
+  int sb = 0;   // ring stage of the chunk's first tap, (T (c - cb0)) % NSW
+  for (int c = cb0; c < ce; ++c) {
     const bf16_t* Pc = lds + (c & 1) * PATCH;
-    const bool more = c + 1 < nch;
+    const bool more = c + 1 < ce;
     // the patch offset of tap (dr, ds) is (dr + ca) PC + ds + cb
     const int ca = GK == G_S2 ? 1 - ((c >> 1) & 1) : pa, cb = GK == G_S2 ? 1 - (c & 1) : pb;
     // activation fragments (both 16-channel halves) of tap t at patch offset qo
@@ -618,16 +651,76 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_halo(CfK k
     });
     sb = (sb + T) % NSW;
   }
-  conv_epilogue<WN, WM, TN, TM, GK == G_SUB ? G_SUB : G_DIRECT>(k, acc, lds, m0, n0, wn, wm, wave, lane, pa, pb);
+  conv_epilogue<WN, WM, TN, TM, GK == G_SUB ? G_SUB : G_DIRECT>(k, acc, lds, m0, n0, wn, wm, wave, lane, pa, pb,
+                                                                blk.split);
+}
+
+// Sum of a split conv's partials and the conv epilogue: part [splits][Mo][Np]
+// raw fp32 sums at the output pixels; a thread owns eight channels of one
+// pixel (as in conv_epilogue, whose arithmetic it repeats) and adds the
+// splits in order.
+struct CfFin {
+  const float* part;
+  int64_t stride;       // floats between splits
+  int splits, Np, n8;   // n8: 8-channel runs of the output, Mo * yC / 8
+  int H, W;             // the output's grid (for the half-resolution residual)
+  FastDiv fdC8, fdW, fdH;
+  ConvOut o;
+};
+__global__ __launch_bounds__(256) void k_conv_split_fin(CfFin k) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= k.n8) return;
+  const ConvOut& o = k.o;
+  const int m = (int)fdiv((uint32_t)i, k.fdC8);
+  const int n = (i - m * (int)k.fdC8.d) * 8;
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (n < k.Np) {
+    const float* p = k.part + (int64_t)m * k.Np + n;
+#pragma unroll 4
+    for (int s = 0; s < k.splits; ++s, p += k.stride) {
+      float t[8];
+      load8(p, true, 0, t);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += t[e];
+    }
+  }
+  const float accs = (o.acc_scale ? *o.acc_scale : 1.f) * o.acc_mul / (o.acc_div ? *o.acc_div : 1.f);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = v[e] * accs + (o.bias && n + e < o.n_real ? o.bias[n + e] : 0.f);
+  if (o.mask) {
+    float mk[8];
+    load8(o.mask, o.mask_f32, m * o.maskC + n, mk);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = mk[e] > 0.f ? v[e] : 0.f;
+  }
+  if (o.res_mode != R_NONE) {
+    int ri = m;
+    if (o.res_mode == R_HALF) {
+      const int t = (int)fdiv((uint32_t)m, k.fdW), ow = m - t * k.W;
+      const int b = (int)fdiv((uint32_t)t, k.fdH), oh = t - b * k.H;
+      ri = (b * (k.H >> 1) + (oh >> 1)) * (k.W >> 1) + (ow >> 1);
+    }
+    float rv[8];
+    load8(o.res, o.res_f32, ri * o.resC + n, rv);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += o.res_scale * rv[e];
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    if (n + e >= o.n_real) v[e] = 0.f;
+  if (o.y_f32) {
+    float* yp = (float*)o.y + m * o.yC + n;
+    *reinterpret_cast<float4*>(yp) = make_float4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<float4*>(yp + 4) = make_float4(v[4], v[5], v[6], v[7]);
+  } else {
+    *reinterpret_cast<uint4*>((bf16_t*)o.y + m * o.yC + n) = pack8(v);
+  }
 }
 
 template <int WN, int WM, int TN, int TM, int PPX, int GK>
 std::string launch_halo(hipStream_t s, CfK& k, bool relu) {
   constexpr int BN = WN * TN * 32, BM = WM * TM * 32;
-  k.tiles_m = (int)cdiv(k.M, BM);
-  k.tiles_n = (int)cdiv(k.Np, BN);
-  k.ksteps = (GK == G_DIRECT ? 9 : GK == G_S2 ? 16 : 4) * (k.C / 32);
-  dim3 grid(k.tiles_m * k.tiles_n * (GK == G_SUB ? 4 : 1)), block(64 * WN * WM);
+  dim3 grid(k.tiles_m * k.tiles_n * (GK == G_SUB ? 4 : 1) * k.splits), block(64 * WN * WM);
   const std::string name = "k_conv_halo<" + std::to_string(BN) + "x" + std::to_string(BM) +
                            (GK == G_SUB ? ",G_SUB" : GK == G_S2 ? ",G_S2" : "") + (relu ? ",true>" : ",false>");
   if constexpr (GK != G_SUB) {
@@ -647,19 +740,14 @@ inline int halo_patch(int BM, int H, int W) {
   return (BM / W + 2) * (W + 2);
 }
 
-template <int WN, int WM, int TN, int TM, int NS = 3, int KS = 32>
+template <int WN, int WM, int TN, int TM>
 std::string launch_cfg(hipStream_t s, CfK& k, int gather, bool relu) {
   constexpr int BN = WN * TN * 32, BM = WM * TM * 32;
-  if (k.C % KS) throw Error{-2, "conv_fwd: channels per step"};
-  k.ksteps = k.R * k.R * (k.C / KS);
-  k.tiles_m = (int)cdiv(k.M, BM);
-  k.tiles_n = (int)cdiv(k.Np, BN);
-  dim3 grid(k.tiles_m * k.tiles_n * (gather == G_SUB ? 4 : 1)), block(64 * WN * WM);
+  dim3 grid(k.tiles_m * k.tiles_n * (gather == G_SUB ? 4 : 1) * k.splits), block(64 * WN * WM);
 #define PG_CF_CASE(G, R_)                                                             \
   if (gather == G && relu == R_) {                                                    \
-    hipLaunchKernelGGL((k_conv_fwd<WN, WM, TN, TM, NS, KS, G, R_>), grid, block, 0, s, k); \
-    return "k_conv_fwd<" + std::to_string(BN) + "x" + std::to_string(BM) + (KS == 32 ? "" : "k" + std::to_string(KS)) + \
-           (NS == 3 ? "" : "/" + std::to_string(NS)) + "," #G "," #R_ ">"; \
+    hipLaunchKernelGGL((k_conv_fwd<WN, WM, TN, TM, 3, 32, G, R_>), grid, block, 0, s, k); \
+    return "k_conv_fwd<" + std::to_string(BN) + "x" + std::to_string(BM) + "," #G "," #R_ ">"; \
   }
   PG_CF_CASE(G_DIRECT, false)
   PG_CF_CASE(G_DIRECT, true)
@@ -670,6 +758,124 @@ std::string launch_cfg(hipStream_t s, CfK& k, int gather, bool relu) {
   PG_CF_CASE(G_SUB, false)
 #undef PG_CF_CASE
   throw Error{-2, "conv_fwd: unsupported gather"};
+}
+
+// The kernel and tile of a conv, and the split of its K loop.
+enum CfKernel { kRing, kHaloDirect, kHaloSub, kHaloS2 };
+struct CfPlan {
+  int kernel, bn, bm;
+  int tiles_m, tiles_n, ksteps;
+  int splits, per;
+};
+
+// Tile choice (measured on the BigGAN shapes in the train step).  For
+// multiples of 256 channels an eight-wave block (one per CU) on a 256 x
+// 256 tile halves the operand bytes per MFMA of the four-wave 128 x 256
+// tile, and wins whenever its blocks come in whole rounds over the CUs
+// (the last round at least three quarters full); with a ragged last round
+// the four-wave tiles, two per CU, spread better.  Otherwise: 128 x 256
+// for multiples of 128 (128 x 128 for exactly 128, the 1x1 attention
+// projections with K <= 192), 192 x 128 for multiples of 192, 96 x 256
+// for the other multiples of 96, and 32 / 64 x 256 for narrow outputs.
+// Direct 3x3 convs whose tiles are whole image rows take the halo kernel
+// (each activation chunk loaded once for all nine taps) on the 256 x 256
+// and 192 x 128 tiles, and for 96 channels on an eight-wave 96 x 512 tile,
+// whose weight loads the wider tile amortises (measured: on the four-wave
+// 128 x 256 tile the patch addressing of its four pixel fragments costs
+// more than the loads it saves).
+void cf_tile(int gather, int64_t M, int H, int W, int R, int C, int Np, CfPlan& p) {
+  const int par = gather == G_SUB ? 4 : 1;
+  auto set = [&](int kernel, int bn, int bm) {
+    p.kernel = kernel;
+    p.bn = bn;
+    p.bm = bm;
+  };
+  const bool halo = gather == G_DIRECT && R == 3;
+  auto fits = [&](int bm, int ppx) {
+    const int np = halo_patch(bm, H, W);
+    return halo && np > 0 && np <= ppx;
+  };
+  const int64_t tiles8 = cdiv(M, 256) * (Np / 256) * par;
+  const int64_t last8 = tiles8 % 256;
+  if (Np % 256 == 0 && tiles8 >= 192 && (last8 == 0 || last8 >= 192))
+    return set(fits(256, 384) ? kHaloDirect : kRing, 256, 256);
+  if (Np % 192 == 0 && fits(128, 320)) return set(kHaloDirect, 192, 128);
+  if (Np == 96 && fits(512, 896)) return set(kHaloDirect, 96, 512);
+  // sub-pixel convs (a 2x2 filter per parity over the source grid) share the
+  // patch logic, over a 96 x 256 tile and, for multiples of 192 with K = 4 C
+  // of at least 768, a 192 x 128 one (measured: 3-7% faster than the ring
+  // kernel's tiles on the BigGAN shapes down to that K)
+  const bool hsub = gather == G_SUB && R == 2;
+  auto fits_sub = [&](int bm, int ppx) {
+    const int np = halo_patch(bm, H, W);
+    return hsub && np > 0 && np <= ppx;
+  };
+  if (Np % 192 == 0 && C >= 192 && fits_sub(128, 320)) return set(kHaloSub, 192, 128);
+  if (Np == 96 && fits_sub(256, 448)) return set(kHaloSub, 96, 256);
+  // the stride-2 4x4 filter (pooled D conv2): a patch per parity class of the source
+  const bool hs2 = gather == G_S2 && R == 4;
+  auto fits_s2 = [&](int bm, int ppx) {
+    const int np = halo_patch(bm, H, W);
+    return hs2 && np > 0 && np <= ppx;
+  };
+  if (Np % 192 == 0 && fits_s2(128, 320)) return set(kHaloS2, 192, 128);
+  if (Np == 96 && fits_s2(256, 448)) return set(kHaloS2, 96, 256);
+  // eight waves on 192 x 256 where those tiles come in whole rounds over
+  // the CUs and the four-wave tiles would not
+  if (Np % 192 == 0) {
+    const int64_t t6 = cdiv(M, 256) * (Np / 192) * par, l6 = t6 % 256;
+    const int64_t t4 = cdiv(M, Np % 128 == 0 ? 256 : 128) * (Np % 128 == 0 ? Np / 128 : Np / 192) * par,
+                  l4 = t4 % 512;
+    if (t6 >= 192 && (l6 == 0 || l6 >= 192) && l4 != 0 && l4 < 384) return set(kRing, 192, 256);
+  }
+  if (Np == 128) return set(kRing, 128, 128);
+  if (Np % 128 == 0) return M <= 128 ? set(kRing, 128, 128) : set(kRing, 128, 256);
+  if (Np % 192 == 0) return set(kRing, 192, 128);
+  if (Np % 96 == 0) return set(kRing, 96, 256);
+  if (Np <= 32) return set(kRing, 32, 256);
+  if (Np <= 64) return set(kRing, 64, 256);
+  set(kRing, 128, 128);
+}
+
+// bytes of one split's partials
+int64_t split_bytes(int gather, int64_t M, int Np) { return 4 * M * (gather == G_SUB ? 4 : 1) * Np; }
+
+// Split of K: a conv whose tiles leave half of the CUs or more without a
+// block (the deep layers at small batches: few pixels, thousands of K steps)
+// is split over K, as far as its blocks still run at once, at least eight
+// K steps each; k_conv_split_fin sums the fp32 partials in split order.  At
+// most 256 blocks of 64 K sums each, so the partials take 64 MB at most.
+// Modelled cost of s splits: the K steps of one block (0.6 us per 32-deep
+// step of a 128 x 256 tile with the chip full), a second launch (5 us) and
+// the partials written and read (4 TB/s).  Measured on the 1536-channel 3x3
+// conv at 1024 pixels (432 steps, 48 tiles): 191 us in one split, 57 + 8 us
+// in five (halving or doubling the model's constants moves whole blocks by
+// less than 2 %; more splits than CUs, or the 256 x 256 tile: no gain).
+constexpr int kCUs = 256, kSplitSteps = 8;
+CfPlan cf_plan(int gather, int64_t M, int H, int W, int R, int C, int Np) {
+  CfPlan p{};
+  cf_tile(gather, M, H, W, R, C, Np, p);
+  p.tiles_m = (int)cdiv(M, p.bm);
+  p.tiles_n = (int)cdiv(Np, p.bn);
+  p.ksteps = R * R * (C / 32);
+  // units of the K loop: steps (ring), chunks of a tap set (halo)
+  const int taps = p.kernel == kRing ? 1 : (p.kernel == kHaloDirect ? 9 : 4);
+  const int units = p.ksteps / taps;
+  const int64_t blocks = (int64_t)p.tiles_m * p.tiles_n * (gather == G_SUB ? 4 : 1);
+  const double step = 0.6 * taps * (double)p.bn * p.bm / 32768.0;
+  const double part = 2.0 * (double)split_bytes(gather, M, Np) / 4e6;
+  int64_t s = 1;
+  double best = units * step;
+  for (int64_t c = 2; c * blocks <= kCUs && c * cdiv(kSplitSteps, taps) <= units; ++c) {
+    const double t = (double)cdiv(units, c) * step + 5.0 + (double)c * part;
+    if (t < 0.95 * best) {
+      best = t;
+      s = c;
+    }
+  }
+  p.per = (int)cdiv(units, s);
+  p.splits = (int)cdiv(units, p.per);
+  return p;
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -695,8 +901,15 @@ bool conv_fwd_mfma_ok(const ConvIn& in, int H, int W, int R, int Np, const ConvO
   return true;
 }
 
+size_t conv_split_ws(int gather, int B, int H, int W, int R, int C, int Np) {
+  const int64_t M = (int64_t)B * H * W;
+  if (M <= 0) return 0;
+  const CfPlan p = cf_plan(gather, M, H, W, R, C, Np);
+  return p.splits > 1 ? align256((size_t)(p.splits * split_bytes(gather, M, Np))) : 0;
+}
+
 std::string conv_fwd_mfma(hipStream_t s, const ConvIn& in, int H, int W, int R, const void* w, int Np,
-                          const ConvOut& out) {
+                          const ConvOut& out, void* part, size_t part_bytes) {
   CfK k;
   k.x = (const bf16_t*)in.x;
   k.w = (const bf16_t*)w;
@@ -711,72 +924,74 @@ std::string conv_fwd_mfma(hipStream_t s, const ConvIn& in, int H, int W, int R, 
   k.pad = in.gather == G_S2 ? (R - 2) / 2 : R / 2;
   k.M = (int)((int64_t)in.B * H * W);
   k.Np = Np;
-  k.ksteps = R * R * (in.C / 32);
   k.fdW = make_fastdiv(W);
   k.fdH = make_fastdiv(H);
   k.o = out;
-  // Tile choice (measured on the BigGAN shapes in the train step).  For
-  // multiples of 256 channels an eight-wave block (one per CU) on a 256 x
-  // 256 tile halves the operand bytes per MFMA of the four-wave 128 x 256
-  // tile, and wins whenever its blocks come in whole rounds over the CUs
-  // (the last round at least three quarters full); with a ragged last round
-  // the four-wave tiles, two per CU, spread better.  Otherwise: 128 x 256
-  // for multiples of 128 (128 x 128 for exactly 128, the 1x1 attention
-  // projections with K <= 192), 192 x 128 for multiples of 192, 96 x 256
-  // for the other multiples of 96, and 32 / 64 x 256 for narrow outputs.
-  // Direct 3x3 convs whose tiles are whole image rows take the halo kernel
-  // (each activation chunk loaded once for all nine taps) on the 256 x 256
-  // and 192 x 128 tiles, and for 96 channels on an eight-wave 96 x 512 tile,
-  // whose weight loads the wider tile amortises (measured: on the four-wave
-  // 128 x 256 tile the patch addressing of its four pixel fragments costs
-  // more than the loads it saves).
-  const bool halo = in.gather == G_DIRECT && R == 3;
-  auto fits = [&](int bm, int ppx) {
-    const int np = halo_patch(bm, H, W);
-    return halo && np > 0 && np <= ppx;
-  };
-  const int64_t tiles8 = cdiv(k.M, 256) * (Np / 256) * (in.gather == G_SUB ? 4 : 1);
-  const int64_t last8 = tiles8 % 256;
-  if (Np % 256 == 0 && tiles8 >= 192 && (last8 == 0 || last8 >= 192))
-    return fits(256, 384) ? launch_halo<2, 4, 4, 2, 384, G_DIRECT>(s, k, in.relu)
-                          : launch_cfg<2, 4, 4, 2>(s, k, in.gather, in.relu);
-  if (Np % 192 == 0 && fits(128, 320)) return launch_halo<2, 2, 3, 2, 320, G_DIRECT>(s, k, in.relu);
-  if (Np == 96 && fits(512, 896)) return launch_halo<1, 8, 3, 2, 896, G_DIRECT>(s, k, in.relu);
-  // sub-pixel convs (a 2x2 filter per parity over the source grid) share the
-  // patch logic, over a 96 x 256 tile and, for multiples of 192 with K = 4 C
-  // of at least 768, a 192 x 128 one (measured: 3-7% faster than the ring
-  // kernel's tiles on the BigGAN shapes down to that K)
-  const bool hsub = in.gather == G_SUB && R == 2;
-  auto fits_sub = [&](int bm, int ppx) {
-    const int np = halo_patch(bm, H, W);
-    return hsub && np > 0 && np <= ppx;
-  };
-  if (Np % 192 == 0 && in.C >= 192 && fits_sub(128, 320))
-    return launch_halo<2, 2, 3, 2, 320, G_SUB>(s, k, false);
-  if (Np == 96 && fits_sub(256, 448)) return launch_halo<1, 4, 3, 2, 448, G_SUB>(s, k, false);
-  // the stride-2 4x4 filter (pooled D conv2): a patch per parity class of the source
-  const bool hs2 = in.gather == G_S2 && R == 4;
-  auto fits_s2 = [&](int bm, int ppx) {
-    const int np = halo_patch(bm, H, W);
-    return hs2 && np > 0 && np <= ppx;
-  };
-  if (Np % 192 == 0 && fits_s2(128, 320)) return launch_halo<2, 2, 3, 2, 320, G_S2>(s, k, in.relu);
-  if (Np == 96 && fits_s2(256, 448)) return launch_halo<1, 4, 3, 2, 448, G_S2>(s, k, in.relu);
-  // eight waves on 192 x 256 where those tiles come in whole rounds over
-  // the CUs and the four-wave tiles would not
-  if (Np % 192 == 0) {
-    const int64_t t6 = cdiv(k.M, 256) * (Np / 192) * (in.gather == G_SUB ? 4 : 1), l6 = t6 % 256;
-    const int64_t t4 = cdiv(k.M, Np % 128 == 0 ? 256 : 128) * (Np % 128 == 0 ? Np / 128 : Np / 192) *
-                       (in.gather == G_SUB ? 4 : 1), l4 = t4 % 512;
-    if (t6 >= 192 && (l6 == 0 || l6 >= 192) && l4 != 0 && l4 < 384) return launch_cfg<2, 4, 3, 2>(s, k, in.gather, in.relu);
+  CfPlan p = cf_plan(in.gather, k.M, H, W, R, in.C, Np);
+  const int64_t sb = split_bytes(in.gather, k.M, Np);
+  if (p.splits > 1 && (!part || (size_t)(p.splits * sb) > part_bytes)) {
+    // no scratch for the partials: one split
+    p.per *= p.splits;
+    p.splits = 1;
   }
-  if (Np == 128) return launch_cfg<2, 2, 2, 2>(s, k, in.gather, in.relu);
-  if (Np % 128 == 0) return launch_cfg<2, 2, 2, 4>(s, k, in.gather, in.relu);
-  if (Np % 192 == 0) return launch_cfg<2, 2, 3, 2>(s, k, in.gather, in.relu);
-  if (Np % 96 == 0) return launch_cfg<1, 4, 3, 2>(s, k, in.gather, in.relu);
-  if (Np <= 32) return launch_cfg<1, 4, 1, 2>(s, k, in.gather, in.relu);
-  if (Np <= 64) return launch_cfg<1, 4, 2, 2>(s, k, in.gather, in.relu);
-  return launch_cfg<2, 2, 2, 2>(s, k, in.gather, in.relu);
+  k.tiles_m = p.tiles_m;
+  k.tiles_n = p.tiles_n;
+  k.ksteps = p.ksteps;
+  k.splits = p.splits;
+  k.per = p.per;
+  k.split_stride = p.splits > 1 ? sb / 4 : 0;
+  if (p.splits > 1) {
+    PG_CHECK(aligned16(part) && Np % 8 == 0, "conv_fwd: split partials must be 16-byte aligned rows of 8");
+    k.o = ConvOut{};
+    k.o.y = part;
+    k.o.y_f32 = 1;
+    k.o.yC = Np;
+    k.o.n_real = Np;
+  }
+  const int tile = p.bn * 1000 + p.bm;
+  std::string name;
+  if (p.kernel == kHaloDirect) {
+    name = tile == 256256   ? launch_halo<2, 4, 4, 2, 384, G_DIRECT>(s, k, in.relu)
+           : tile == 192128 ? launch_halo<2, 2, 3, 2, 320, G_DIRECT>(s, k, in.relu)
+                            : launch_halo<1, 8, 3, 2, 896, G_DIRECT>(s, k, in.relu);
+  } else if (p.kernel == kHaloSub) {
+    name = tile == 192128 ? launch_halo<2, 2, 3, 2, 320, G_SUB>(s, k, false)
+                          : launch_halo<1, 4, 3, 2, 448, G_SUB>(s, k, false);
+  } else if (p.kernel == kHaloS2) {
+    name = tile == 192128 ? launch_halo<2, 2, 3, 2, 320, G_S2>(s, k, in.relu)
+                          : launch_halo<1, 4, 3, 2, 448, G_S2>(s, k, in.relu);
+  } else {
+    switch (tile) {
+      case 256256: name = launch_cfg<2, 4, 4, 2>(s, k, in.gather, in.relu); break;
+      case 192256: name = launch_cfg<2, 4, 3, 2>(s, k, in.gather, in.relu); break;
+      case 128128: name = launch_cfg<2, 2, 2, 2>(s, k, in.gather, in.relu); break;
+      case 128256: name = launch_cfg<2, 2, 2, 4>(s, k, in.gather, in.relu); break;
+      case 192128: name = launch_cfg<2, 2, 3, 2>(s, k, in.gather, in.relu); break;
+      case 96256: name = launch_cfg<1, 4, 3, 2>(s, k, in.gather, in.relu); break;
+      case 32256: name = launch_cfg<1, 4, 1, 2>(s, k, in.gather, in.relu); break;
+      case 64256: name = launch_cfg<1, 4, 2, 2>(s, k, in.gather, in.relu); break;
+      default: throw Error{-2, "conv_fwd: no kernel for the planned tile"};
+    }
+  }
+  if (p.splits > 1) {
+    PG_LAUNCH_CHECK();
+    const int up = in.gather == G_SUB ? 2 : 1;
+    CfFin f;
+    f.part = (const float*)part;
+    f.stride = sb / 4;
+    f.splits = p.splits;
+    f.Np = Np;
+    f.n8 = (int)((int64_t)k.M * up * up * (out.yC / 8));
+    f.H = H * up;
+    f.W = W * up;
+    f.fdC8 = make_fastdiv(out.yC / 8);
+    f.fdW = make_fastdiv(f.W);
+    f.fdH = make_fastdiv(f.H);
+    f.o = out;
+    hipLaunchKernelGGL(k_conv_split_fin, dim3((unsigned)cdiv(f.n8, 256)), dim3(256), 0, s, f);
+    name += "/split";
+  }
+  return name;
 }
 
 }  // namespace pg

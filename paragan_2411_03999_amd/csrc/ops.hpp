@@ -61,14 +61,18 @@ struct ConvOut {
 
 // y = conv_RxR(gathered/transformed x, w) on an H x W grid (stride 1, pad R/2).
 // w: packed [Np][R][R][in.C] in the activation type (bf16 or fp32).
+// part (conv_split_ws bytes, 16-byte aligned; may be null): scratch for the
+// fp32 partials of a conv whose K loop is split over blocks.
 void conv_fwd(hipStream_t s, bool f32, const ConvIn& in, int H, int W, int R,
-              const void* w, int Np, const ConvOut& out);
+              const void* w, int Np, const ConvOut& out, void* part = nullptr, size_t part_bytes = 0);
+// bf16 only (0 for a conv that is not split)
+size_t conv_split_ws(int gather, int B, int H, int W, int R, int C, int Np);
 
 // The MFMA convolution for direct / upsampled operands without a BN-affine
 // prologue (convfwd.hip); conv_fwd dispatches to it when conv_fwd_mfma_ok.
 bool conv_fwd_mfma_ok(const ConvIn& in, int H, int W, int R, int Np, const ConvOut& out);
 std::string conv_fwd_mfma(hipStream_t s, const ConvIn& in, int H, int W, int R, const void* w, int Np,
-                          const ConvOut& out);
+                          const ConvOut& out, void* part, size_t part_bytes);
 
 // Gradient operand of a weight gradient: dy at the conv-output grid (H x W)
 // read directly or as a nearest-2x upsample of a half-resolution tensor.
