@@ -512,69 +512,69 @@ __global__ __launch_bounds__(256) void k_wgrad_fold_sub(const float* __restrict_
   reinterpret_cast<float4*>(dw)[i] = make_float4(acc.x * scale, acc.y * scale, acc.z * scale, acc.w * scale);
 }
 
+// Tiles of k_wgrad_tr, then the two of k_wgrad_row3, with the measured time
+// (us) of one 32-pixel stage of a block: c1 with one block on its CU, c2 in
+// a full round (two four-wave blocks or one eight-wave block per CU).
 struct TrCfg {
   int WM, WN, TM, TN;
+  float c1, c2;
 };
-constexpr TrCfg kTrCfgs[] = {{2, 2, 4, 2}, {2, 2, 2, 4}, {2, 2, 3, 3}, {1, 4, 3, 2}, {1, 4, 3, 3}, {2, 2, 2, 2},
-                             {4, 2, 2, 4}};
-constexpr int kTrWide = 6;   // the eight-wave 256 x 256 tile
+constexpr TrCfg kTrCfgs[] = {{2, 2, 4, 2, 0.82f, 1.19f}, {2, 2, 2, 4, 0.89f, 1.26f}, {2, 2, 3, 3, 0.86f, 1.27f},
+                             {1, 4, 3, 2, 0.84f, 1.12f}, {1, 4, 3, 3, 1.10f, 1.59f}, {2, 2, 2, 2, 0.64f, 0.75f},
+                             {4, 2, 2, 4, 1.08f, 1.10f},
+                             {4, 2, 2, 3, 0.82f, 0.82f}, {2, 2, 3, 3, 0.79f, 1.05f}};
+constexpr int kRow256 = 7, kRow192 = 8, kTrCount = 9;
 
 struct TrPlan {
   int cfg, tiles_n, tiles_k, splits, m_per_split;
 };
 
-// Tile shape with the least padded work (BigGAN widths are multiples of 96,
-// filter-tap K dims multiples of 288), then a split of the pixel range that
-// gives the chip ~4 blocks per CU, each split at least 1024 pixels long.
-TrPlan tr_plan(int64_t M, int R, int Cin, int Np, int n_cu) {
-  const int64_t K = (int64_t)R * R * Cin;
-  TrPlan p{0, 0, 0, 1, 0};
-  double best = 1e300;
-  for (int c = 0; c < (int)(sizeof(kTrCfgs) / sizeof(kTrCfgs[0])); ++c) {
+// whether k_wgrad_row3 can run: whole 32-pixel stages of an image row, 64-channel
+// chunks, tiles of 256 or 192 output channels
+bool row3_shape(int R, int Cin, int Np) {
+  return R == 3 && Cin % 64 == 0 && (Np % 256 == 0 || Np % 192 == 0);
+}
+
+// Tile and split of the pixel range, by modelled time.  Every block runs the
+// same number of stages, so the launch takes the rounds of blocks over the
+// CUs times the stages of a split; a split count whose blocks fill whole
+// rounds is what pays, each further split costs its partial sums a write and
+// a read in the reduction, and a tile costs its padded work through the
+// number of tiles.  (Filling four blocks a CU, whatever the last round:
+// 192 x 192 tiles over 524288 x 384 x 1728, 1026 blocks, 772 us; 504 blocks,
+// 617 us.  1x1 filters on 32 blocks of 32 stages: 40 us, on 216: 20.)
+// row3: the row-tap kernel is a candidate.  classes: parity classes of the
+// sub-pixel form, which share the launch.
+TrPlan tr_plan(int64_t M, int R, int Cin, int Np, int n_cu, bool row3, int classes) {
+  const int64_t K = (int64_t)R * R * Cin, nout = (int64_t)Np * K;
+  const int64_t smax = std::max<int64_t>(1, std::min<int64_t>(M / (2 * kMS), (512LL << 20) / (4 * nout)));
+  TrPlan best{0, 0, 0, 1, 0};
+  double best_t = 1e300;
+  for (int c = 0; c < kTrCount; ++c) {
     const TrCfg& t = kTrCfgs[c];
-    const int bn = t.WM * t.TM * 32, bk = t.WN * t.TN * 32;
-    const double tiles = (double)cdiv(Np, bn) * cdiv(K, bk);
-    const double eff = t.TM * t.TN >= 8 ? 1.0 : (t.TM * t.TN >= 6 ? 0.92 : 0.8);
-    const double cost = tiles * bn * bk / eff;
-    if (cost < best * 0.999) {
-      best = cost;
-      p.cfg = c;
-    }
-  }
-  // 256 x 256 on eight waves (one block per CU) where both dimensions are
-  // multiples of 256: half the operand bytes per MFMA of 256 x 128
-  // (measured 5-13 % faster on the 768 / 1536-channel weight gradients)
-  if (Np % 256 == 0 && K % 256 == 0) p.cfg = kTrWide;
-  const TrCfg& t = kTrCfgs[p.cfg];
-  p.tiles_n = (int)cdiv(Np, t.WM * t.TM * 32);
-  p.tiles_k = (int)cdiv(K, t.WN * t.TN * 32);
-  const int64_t tiles = (int64_t)p.tiles_n * p.tiles_k;
-  const int64_t smax = std::max<int64_t>(1, M / 1024);
-  const int64_t cap = (512LL << 20) / (4 * (int64_t)Np * K);
-  int64_t sp;
-  if (p.cfg == kTrWide) {
-    // ~1 block per CU (each split's partial sums cost a write and a read in
-    // the reduction), then the split count up to twice that whose blocks
-    // fill the last round over the CUs best
-    const int64_t s0 = std::max<int64_t>(1, std::min({cdiv((int64_t)n_cu, tiles), smax, cap}));
-    sp = s0;
-    double best_fill = 0.0;
-    for (int64_t c = s0; c <= std::min({2 * s0, smax, cap}); ++c) {
-      const int64_t b = c * tiles;
-      const double fill = (double)b / (double)(cdiv(b, (int64_t)n_cu) * n_cu);
-      if (fill > best_fill + 1e-9) {
-        best_fill = fill;
-        sp = c;
+    if (c >= kRow256 && (!row3 || (c == kRow256) != (Np % 256 == 0))) continue;
+    const int tn = (int)cdiv(Np, t.WM * t.TM * 32);
+    const int tk = c >= kRow256 ? 3 * (Cin / 64) : (int)cdiv(K, t.WN * t.TN * 32);
+    const bool wide = t.WM * t.WN == 8;
+    const int64_t tiles = (int64_t)tn * tk * classes, cap = (int64_t)n_cu * (wide ? 1 : 2);
+    for (int q = 0; q <= 6; ++q) {
+      // one split; a block on every CU; then 1, 2, 3, 4, 6 full rounds
+      static const int kHalves[] = {0, 1, 2, 4, 6, 8, 12};
+      int64_t s = q == 0 ? 1 : kHalves[q] * cap / 2 / tiles;
+      s = std::max<int64_t>(1, std::min(s, smax));
+      const int64_t mps = cdiv(cdiv(M, s), kMS) * kMS;
+      s = cdiv(M, mps);
+      const int64_t full = tiles * s / cap, rem = tiles * s % cap;
+      const double part = 4e-6 * (double)(s * classes * nout);   // MB of results
+      const double rounds = full * t.c2 + (rem == 0 ? 0.0 : !wide && rem <= n_cu ? t.c1 : t.c2);
+      const double time = (double)(mps / kMS + 2) * rounds + part / 6.0 + (s * classes > 1 ? 5.0 + part / 4.0 : 0.0);
+      if (time < 0.99 * best_t) {
+        best_t = time;
+        best = TrPlan{c, tn, tk, (int)s, (int)mps};
       }
     }
-  } else {
-    sp = cdiv(4LL * n_cu, tiles);
-    sp = std::min<int64_t>(sp, smax);
-    sp = std::max<int64_t>(1, std::min<int64_t>(sp, cap));
   }
-  p.m_per_split = (int)(cdiv(cdiv(M, sp), kMS) * kMS);
-  p.splits = (int)cdiv(M, p.m_per_split);
-  return p;
+  return best;
 }
 
 template <int WM, int WN, int TM, int TN>
@@ -639,9 +639,11 @@ bool wgrad_tr_ok(const GradIn& g, const ConvIn& in, int H, int W, int R, int Np)
          in.C % 8 == 0 && g.C % 8 == 0 && Np % 8 == 0;
 }
 
+// (whether the row-tap kernel can run depends on the image too: room for either plan)
 size_t wgrad_tr_ws(int64_t M, int R, int Cin, int Np, int n_cu) {
-  const TrPlan p = tr_plan(M, R, Cin, Np, n_cu);
-  return p.splits > 1 ? align256((size_t)p.splits * Np * R * R * Cin * 4) : 0;
+  int sp = tr_plan(M, R, Cin, Np, n_cu, false, 1).splits;
+  if (row3_shape(R, Cin, Np)) sp = std::max(sp, tr_plan(M, R, Cin, Np, n_cu, true, 1).splits);
+  return sp > 1 ? align256((size_t)sp * Np * R * R * Cin * 4) : 0;
 }
 
 void wgrad_tr(hipStream_t s, const GradIn& g, const ConvIn& in, int H, int W, int R, int Np, float* dw,
@@ -668,20 +670,14 @@ void wgrad_tr(hipStream_t s, const GradIn& g, const ConvIn& in, int H, int W, in
   k.fdH = make_fastdiv(H);
   k.fdC = make_fastdiv(in.C);
   k.fdR = make_fastdiv(R);
-  const TrPlan p = tr_plan(k.M, R, in.C, Np, n_cu);
+  // the row-tap form (k_wgrad_row3): a direct 3x3 conv over images whose
+  // rows are whole 32-pixel stages
+  const bool row3 = row3_shape(R, in.C, Np) && in.gather == G_DIRECT && W % 32 == 0;
+  const TrPlan p = tr_plan(k.M, R, in.C, Np, n_cu, row3, 1);
   k.m_per_split = p.m_per_split;
   k.tiles_n = p.tiles_n;
   k.tiles_k = p.tiles_k;
   k.splits = p.splits;
-  // the row-tap form (k_wgrad_row3): a direct 3x3 conv over images whose
-  // rows are whole 32-pixel stages, 64-channel chunks, 192 / 256-channel
-  // output tiles; same splits (so the same partial buffer)
-  const bool row3 = R == 3 && in.gather == G_DIRECT && W % 32 == 0 && in.C % 64 == 0 &&
-                    (Np % 256 == 0 || Np % 192 == 0) && k.M % 32 == 0;
-  if (row3) {
-    k.tiles_n = Np / (Np % 256 == 0 ? 256 : 192);
-    k.tiles_k = 3 * (in.C / 64);
-  }
   const int64_t nout = (int64_t)Np * k.Kdim;
   if (p.splits > 1 && (size_t)p.splits * nout * 4 > ws_bytes) throw Error{-3, "conv_wgrad: workspace too small"};
   PG_CHECK(p.splits == 1 || (nout % 4 == 0 && (((uintptr_t)ws | (uintptr_t)dw) & 15) == 0),
@@ -693,8 +689,8 @@ void wgrad_tr(hipStream_t s, const GradIn& g, const ConvIn& in, int H, int W, in
   const int gm = g.gather == G_UP2 ? kGUp2 : kGDirect;
   std::string name;
   ProfScope prof(s);
-  if (row3)
-    name = Np % 256 == 0 ? launch_row3<4, 2>(s, k, blocks, gm, in.relu) : launch_row3<2, 3>(s, k, blocks, gm, in.relu);
+  if (p.cfg >= kRow256)
+    name = p.cfg == kRow256 ? launch_row3<4, 2>(s, k, blocks, gm, in.relu) : launch_row3<2, 3>(s, k, blocks, gm, in.relu);
   else
     name = launch_cfg_tr(s, p.cfg, k, blocks, gm, in.gather, in.relu);
   PG_LAUNCH_CHECK();
@@ -722,8 +718,7 @@ void wgrad_tr(hipStream_t s, const GradIn& g, const ConvIn& in, int H, int W, in
 // and dW_ab = sum over the class's pixels of dY (x) (the 2x2 window of the
 // source): 4/9 of the upsampled form's MACs, on the unexpanded source.
 static TrPlan sub_plan(int64_t Msrc, int Cin, int Np, int n_cu) {
-  // four parity classes share the CUs
-  return tr_plan(Msrc, 2, Cin, Np, std::max(1, n_cu / 4));
+  return tr_plan(Msrc, 2, Cin, Np, n_cu, false, 4);   // four parity classes share the CUs
 }
 
 size_t wgrad_sub_ws(int64_t Msrc, int Cin, int Np, int n_cu) {

@@ -1,5 +1,6 @@
 """Parity of the launch forms that small problems take: convolutions whose K
-loop is split over blocks.  Sizes at the edges of their tiles: partial pixel
+loop is split over blocks, weight gradients planned in whole rounds of
+blocks.  Sizes at the edges of their tiles: partial pixel
 and channel tiles, uneven last splits, every gather and epilogue of a split
 conv.  Same oracle and bars as the block tests."""
 import pytest
@@ -40,3 +41,15 @@ def test_split_conv(kind, shape, names):
     run(dtype=lib.BF16, seed=700, weights="gaussian", **shape)
     for n in names:
         assert n in parity.SEEN, (n, launched("split"))
+
+
+# Weight-gradient plans: row-tap tiles on a two-row image, a pixel range that
+# ends inside a stage and inside the last split, fewer pixels than one split
+@pytest.mark.parametrize("kind,shape", [
+    ("d", dict(B=1, H=2, W=32, cin=64, cout=256, preact=True, down=False, lsc=True)),
+    ("d", dict(B=2, H=33, W=31, cin=96, cout=192, preact=True, down=False, lsc=True)),
+    ("g", dict(B=1, H=3, W=3, cin=64, cout=384, dc=20)),
+])
+def test_wgrad_plan(kind, shape):
+    run = run_gblock if kind == "g" else run_dblock
+    run(dtype=lib.BF16, seed=710, weights="gaussian", **shape)
