@@ -487,29 +487,51 @@ __global__ __launch_bounds__(1024) void k_wgtr_reduce_wide(const float* __restri
 //   dw[n][r][s][c] = scale * sum over parities (a, b), then splits, of
 //                    part[(2a + b) * splits + sp][n][(D_a(r) * 2 + D_b(s)) * C + c],
 // D_0 = (0, 1, 1), D_1 = (0, 0, 1): the 2x2 tap that 3x3 tap r feeds in
-// parity class a.  Four consecutive channels per thread (C % 4 == 0).
-__global__ __launch_bounds__(256) void k_wgrad_fold_sub(const float* __restrict__ part, int splits, int Np, int C,
-                                                        float scale, float* __restrict__ dw) {
+// parity class a.  Four consecutive channels per thread (C % 4 == 0).  WV
+// waves share an output's splits (wave w the splits w, w + WV, .. of every
+// class), combined in wave order: with one wave a narrow filter's few
+// outputs read hundreds of partials in series (96 x 192 channels, 57 splits:
+// 176 us on 162 blocks; on 16 waves 20).
+template <int WV>
+__global__ __launch_bounds__(WV == 1 ? 256 : WV * 64) void k_wgrad_fold_sub(const float* __restrict__ part, int splits,
+                                                                            int Np, int C, float scale,
+                                                                            float* __restrict__ dw) {
+  __shared__ float4 sh[WV][64];
   const int C4 = C / 4;
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)Np * 9 * C4) return;
+  const int lane = threadIdx.x & 63, wv = WV == 1 ? 0 : (int)threadIdx.x >> 6;
+  const int64_t i = WV == 1 ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)blockIdx.x * 64 + lane;
+  const bool on = i < (int64_t)Np * 9 * C4;
   const int c4 = (int)(i % C4);
   const int64_t t = i / C4;
   const int tap = (int)(t % 9), n = (int)(t / 9);
   const int r = tap / 3, s_ = tap % 3;
   const int64_t plane = (int64_t)Np * 4 * C;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (on) {
 #pragma unroll
-  for (int ab = 0; ab < 4; ++ab) {
-    const int a = ab >> 1, b = ab & 1;
-    const int du = a == 0 ? (r > 0) : (r == 2), dv = b == 0 ? (s_ > 0) : (s_ == 2);
-    const float* src = part + (int64_t)ab * splits * plane + ((int64_t)n * 4 + du * 2 + dv) * C + 4 * c4;
-    for (int sp = 0; sp < splits; ++sp) {
-      const float4 v = *reinterpret_cast<const float4*>(src + sp * plane);
-      acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+    for (int ab = 0; ab < 4; ++ab) {
+      const int a = ab >> 1, b = ab & 1;
+      const int du = a == 0 ? (r > 0) : (r == 2), dv = b == 0 ? (s_ > 0) : (s_ == 2);
+      const float* src = part + (int64_t)ab * splits * plane + ((int64_t)n * 4 + du * 2 + dv) * C + 4 * c4;
+#pragma unroll 4
+      for (int sp = wv; sp < splits; sp += WV) {
+        const float4 v = *reinterpret_cast<const float4*>(src + sp * plane);
+        acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+      }
     }
   }
-  reinterpret_cast<float4*>(dw)[i] = make_float4(acc.x * scale, acc.y * scale, acc.z * scale, acc.w * scale);
+  if (WV > 1) {
+    sh[wv][lane] = acc;
+    __syncthreads();
+    if (wv != 0) return;
+    acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < WV; ++w) {
+      acc.x += sh[w][lane].x; acc.y += sh[w][lane].y; acc.z += sh[w][lane].z; acc.w += sh[w][lane].w;
+    }
+  }
+  if (on)
+    reinterpret_cast<float4*>(dw)[i] = make_float4(acc.x * scale, acc.y * scale, acc.z * scale, acc.w * scale);
 }
 
 // Tiles of k_wgrad_tr, then the two of k_wgrad_row3, with the measured time
@@ -779,8 +801,12 @@ void wgrad_sub(hipStream_t s, const GradIn& g, const ConvIn& in, int Np, float* 
   prof.done(name, flops, 4LL * k.M, Np, k.Kdim);
   ProfScope pr(s);
   const int64_t n4 = (int64_t)Np * 9 * in.C / 4;
-  hipLaunchKernelGGL(k_wgrad_fold_sub, dim3((unsigned)cdiv(n4, 256)), dim3(256), 0, s, (const float*)k.part,
-                     p.splits, Np, in.C, g.gscale, dw);
+  if (p.splits >= 8)   // fewer splits: enough outputs to fill the chip with a thread each
+    hipLaunchKernelGGL(k_wgrad_fold_sub<16>, dim3((unsigned)cdiv(n4, 64)), dim3(1024), 0, s, (const float*)k.part,
+                       p.splits, Np, in.C, g.gscale, dw);
+  else
+    hipLaunchKernelGGL(k_wgrad_fold_sub<1>, dim3((unsigned)cdiv(n4, 256)), dim3(256), 0, s, (const float*)k.part,
+                       p.splits, Np, in.C, g.gscale, dw);
   PG_LAUNCH_CHECK();
   pr.done("k_wgrad_fold_sub", 0.0);
 }
