@@ -389,12 +389,13 @@ void GBlock::bwd(const Exec& ex, const Params& P, const void* x, const float* co
                        {"bn2.gain", w.dg2, cout, 3}, {"bn2.bias", w.db2, cout, 4}};
   const int Cps[4] = {Cip, Cip, Cop, Cop};
   SnBwdJob jobs[7];
+  CbnMap maps[4];
   for (int i = 0; i < 4; ++i) {
     const Lin& l = lins[i];
-    cbn_linear_bwd(ex.st, l.dgb, B, l.C, Cps[i], cond, dc, P.w(l.name), sn[l.slot].sigma, w.dlin[i], dcond,
-                   dcond_acc || i > 0, w.lin);
+    maps[i] = CbnMap{l.dgb, P.w(l.name), sn[l.slot].sigma, w.dlin[i], l.C, Cps[i]};
     jobs[i] = sn_bwd_job(P, l.name, sn[l.slot], w.dlin[i], 1, dc, nullptr);
   }
+  cbn_linear_bwd(ex.st, maps, 4, B, cond, dc, dcond, dcond_acc, w.lin);
   jobs[4] = sn_bwd_job(P, "conv1.w", sn[2], w.dwp1, 3, Cip, nullptr);
   jobs[5] = sn_bwd_job(P, "conv2.w", sn[5], w.dwp2, 3, Cop, nullptr);
   jobs[6] = sn_bwd_job(P, "sc.w", sn[6], w.dwpsc, 1, Cip, nullptr);

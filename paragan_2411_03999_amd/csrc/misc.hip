@@ -1146,114 +1146,63 @@ __global__ void k_cbn_tables(const float* cond, int dc, const float* Wg, const f
   scale[i] = c < C ? g * rstd[c] : 0.f;
 }
 
-// Small fp32 GEMM for the conditional-BN linear maps (B x dc by dc x C and
-// their transposes): C[i][j] = sum_k A(i, k) B(k, j) [/ *div] [+ C[i][j]],
-// A(i, k) = A[i * sai + k * sak], B(k, j) = B[k * sbk + j * sbj].  32 x 32
-// tiles through LDS, k in chunks of 32, fixed summation order.  With a
-// split of K (blockIdx.z; part != nullptr) each split writes its raw sums
-// to part[z][M][N] and k_gemm_reduce adds them in split order.
-__global__ __launch_bounds__(256) void k_gemm_small(int M, int N, int K, const float* A, int64_t sai,
-                                                    int64_t sak, const float* Bm, int64_t sbk, int64_t sbj,
-                                                    float* Cm, int64_t ldc, const float* div, int acc, int kper,
-                                                    float* part) {
-  __shared__ float As[32][33], Bs[32][33];
-  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int kb = blockIdx.z * kper, ke = min(K, kb + kper);
-  float c[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = kb; k0 < ke; k0 += 32) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = ty + 8 * q;
-      // the lane index runs along whichever dimension is contiguous
-      int ai, ak;
-      if (sak == 1) { ai = r; ak = tx; } else { ai = tx; ak = r; }
-      As[ai][ak] = (i0 + ai < M && k0 + ak < ke) ? A[(i0 + ai) * sai + (int64_t)(k0 + ak) * sak] : 0.f;
-      int bk, bj;
-      if (sbj == 1) { bk = r; bj = tx; } else { bk = tx; bj = r; }
-      Bs[bk][bj] = (k0 + bk < ke && j0 + bj < N) ? Bm[(int64_t)(k0 + bk) * sbk + (j0 + bj) * sbj] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < 32; ++kk) {
-      const float b = Bs[kk][tx];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) c[q] = fmaf(As[ty + 8 * q][kk], b, c[q]);
-    }
-    __syncthreads();
-  }
-  const int j = j0 + tx;
-  if (j >= N) return;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int i = i0 + ty + 8 * q;
-    if (i >= M) continue;
-    if (part) {
-      part[((int64_t)blockIdx.z * M + i) * N + j] = c[q];
-      continue;
-    }
-    float v = div ? c[q] / *div : c[q];
-    if (acc) v += Cm[(int64_t)i * ldc + j];
-    Cm[(int64_t)i * ldc + j] = v;
-  }
-}
-
-__global__ void k_gemm_reduce(int M, int N, int splits, const float* part, float* Cm, int64_t ldc,
-                              const float* div, int acc) {
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (int64_t)M * N) return;
-  const int i = (int)(e / N), j = (int)(e - (int64_t)i * N);
-  float sum = 0.f;
-  for (int z = 0; z < splits; ++z) sum += part[(int64_t)z * M * N + e];
-  float v = div ? sum / *div : sum;
-  if (acc) v += Cm[(int64_t)i * ldc + j];
-  Cm[(int64_t)i * ldc + j] = v;
-}
-
-static void gemm_small(hipStream_t st, int M, int N, int K, const float* A, int64_t sai, int64_t sak,
-                       const float* Bm, int64_t sbk, int64_t sbj, float* Cm, int64_t ldc, const float* div,
-                       bool acc, float* part = nullptr, int splits = 1) {
-  if (M <= 0 || N <= 0) return;
-  if (!part || splits <= 1) {
-    hipLaunchKernelGGL(k_gemm_small, dim3((unsigned)cdiv(N, 32), (unsigned)cdiv(M, 32)), dim3(256), 0, st, M, N, K,
-                       A, sai, sak, Bm, sbk, sbj, Cm, ldc, div, (int)acc, K, (float*)nullptr);
-    return;
-  }
-  const int kper = (int)cdiv(cdiv(K, splits), 32) * 32;
-  splits = (int)cdiv(K, kper);
-  hipLaunchKernelGGL(k_gemm_small, dim3((unsigned)cdiv(N, 32), (unsigned)cdiv(M, 32), (unsigned)splits), dim3(256),
-                     0, st, M, N, K, A, sai, sak, Bm, sbk, sbj, Cm, ldc, div, (int)acc, kper, part);
-  hipLaunchKernelGGL(k_gemm_reduce, dim3((unsigned)cdiv((int64_t)M * N, 256)), dim3(256), 0, st, M, N, splits, part,
-                     Cm, ldc, div, (int)acc);
-}
-
 // Both conditional-BN linear maps of one BN in one launch (blockIdx.z: 0
 // gain, 1 bias), written as the tables the conv prologue and BN backward use:
 //   gain[b][c] = 1 + cond[b] . Wg[c] / sigma_g,  scale = gain * rstd[c],
 //   bias[b][c] = cond[b] . Wb[c] / sigma_b,  zeros for c >= C (up to Cp).
-// Same 32 x 32 tiling and summation order as k_gemm_small.
+// The launch is latency-bound (a few MB): tiles are 16 samples x 32
+// channels, and a tile's whole operands -- up to 160 conditioning values a
+// row, BigGAN's 148 -- are staged at once, so a block waits for memory once
+// per 160 values (32 samples x 192 channels: 19 us in 32-deep steps, 6 so).
+constexpr int kCbnK = 160, kCbnB = 16, kCbnC = 32, kCbnS = kCbnK + 4;
 __global__ __launch_bounds__(256) void k_cbn_lin(int B, int C, int Cp, int dc, const float* cond, const float* Wg,
                                                  const float* Wb, const float* sg, const float* sb,
                                                  const float* rstd, float* gain, float* bias, float* scale) {
-  __shared__ float As[32][33], Bs[32][33];
+  __shared__ float4 As4[kCbnB * kCbnS / 4], Bs4[kCbnC * kCbnS / 4];
+  float* const As = reinterpret_cast<float*>(As4);
+  float* const Bs = reinterpret_cast<float*>(Bs4);
   const bool isg = blockIdx.z == 0;
   const float* Wm = isg ? Wg : Wb;
-  const int i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  float c[4] = {0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < dc; k0 += 32) {
+  const int i0 = blockIdx.y * kCbnB, j0 = blockIdx.x * kCbnC;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // channel, samples ty and ty + 8
+  float c[2] = {0.f, 0.f};
+  for (int k0 = 0; k0 < dc; k0 += kCbnK) {
+    const int kn = min(kCbnK, dc - k0);
+    float va[kCbnB / 8][kCbnK / 32], vb[kCbnC / 8][kCbnK / 32];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = ty + 8 * q;
-      As[r][tx] = (i0 + r < B && k0 + tx < dc) ? cond[(int64_t)(i0 + r) * dc + k0 + tx] : 0.f;
-      Bs[tx][r] = (k0 + tx < dc && j0 + r < C) ? Wm[(int64_t)(j0 + r) * dc + k0 + tx] : 0.f;
+    for (int q = 0; q < kCbnB / 8; ++q)
+#pragma unroll
+      for (int h = 0; h < kCbnK / 32; ++h) {
+        const int r = i0 + ty + 8 * q, k = tx + 32 * h;
+        va[q][h] = r < B && k < kn ? cond[(int64_t)r * dc + k0 + k] : 0.f;
+      }
+#pragma unroll
+    for (int q = 0; q < kCbnC / 8; ++q)
+#pragma unroll
+      for (int h = 0; h < kCbnK / 32; ++h) {
+        const int r = j0 + ty + 8 * q, k = tx + 32 * h;
+        vb[q][h] = r < C && k < kn ? Wm[(int64_t)r * dc + k0 + k] : 0.f;
+      }
+#pragma unroll
+    for (int h = 0; h < kCbnK / 32; ++h) {
+#pragma unroll
+      for (int q = 0; q < kCbnB / 8; ++q) As[(ty + 8 * q) * kCbnS + tx + 32 * h] = va[q][h];
+#pragma unroll
+      for (int q = 0; q < kCbnC / 8; ++q) Bs[(ty + 8 * q) * kCbnS + tx + 32 * h] = vb[q][h];
     }
     __syncthreads();
-#pragma unroll 8
-    for (int kk = 0; kk < 32; ++kk) {
-      const float b = Bs[kk][tx];
+    const int k4 = (kn + 3) >> 2;   // (zeros past kn)
+#pragma unroll 4
+    for (int k = 0; k < k4; ++k) {
+      const float4 b = Bs4[tx * (kCbnS / 4) + k];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) c[q] = fmaf(As[ty + 8 * q][kk], b, c[q]);
+      for (int q = 0; q < 2; ++q) {
+        const float4 a = As4[(ty + 8 * q) * (kCbnS / 4) + k];
+        c[q] = fmaf(a.x, b.x, c[q]);
+        c[q] = fmaf(a.y, b.y, c[q]);
+        c[q] = fmaf(a.z, b.z, c[q]);
+        c[q] = fmaf(a.w, b.w, c[q]);
+      }
     }
     __syncthreads();
   }
@@ -1261,7 +1210,7 @@ __global__ __launch_bounds__(256) void k_cbn_lin(int B, int C, int Cp, int dc, c
   if (j >= Cp) return;
   const float sig = *(isg ? sg : sb);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
+  for (int q = 0; q < 2; ++q) {
     const int i = i0 + ty + 8 * q;
     if (i >= B) continue;
     const int64_t o = (int64_t)i * Cp + j;
@@ -1280,8 +1229,8 @@ void cbn_tables(hipStream_t st, const float* cond, int dc, const float* Wg, cons
                 const float* rstd, int B, int C, int Cp, float* gain, float* bias, float* scale) {
   if (cond) {
     // gain_raw[b][c] = cond[b] . Wg[c] / sigma_g, bias[b][c] = cond[b] . Wb[c] / sigma_b
-    hipLaunchKernelGGL(k_cbn_lin, dim3((unsigned)cdiv(Cp, 32), (unsigned)cdiv(B, 32), 2), dim3(256), 0, st, B, C, Cp,
-                       dc, cond, Wg, Wb, sg, sb, rstd, gain, bias, scale);
+    hipLaunchKernelGGL(k_cbn_lin, dim3((unsigned)cdiv(Cp, kCbnC), (unsigned)cdiv(B, kCbnB), 2), dim3(256), 0, st, B,
+                       C, Cp, dc, cond, Wg, Wb, sg, sb, rstd, gain, bias, scale);
     PG_LAUNCH_CHECK();
     return;
   }
@@ -1560,18 +1509,133 @@ void bn_bwd(hipStream_t st, bool f32, const float* g, bool g_up2, const void* x,
   PG_LAUNCH_CHECK();
 }
 
-// Linear-map gradients of the conditional BN:
-//   dW[c][j] = sum_b dgb[b][c] cond[b][j]   (gradient of W/sigma; SN bwd follows)
-//   dcond[b][j] (+)= sum_c dgb[b][c] W[c][j] / sigma
-size_t cbn_linear_bwd_ws_bytes(int B, int dc) { return align256((size_t)kLinSplits * B * dc * 4); }
+// Linear-map gradients of a block's conditional BNs, all maps in two launches:
+//   dW_m[c][j] = sum_b dgb_m[b][c] cond[b][j]   (gradient of W_m/sigma_m; SN bwd follows)
+//   dcond[b][j] (+)= sum over maps m of (sum_c dgb_m[b][c] W_m[c][j]) / sigma_m
+// Launch 1 forms every map's dW and the partial sums of dcond, split over c
+// (up to kLinSplits per map), in 32 x 32 tiles with the next 64-deep K chunk
+// in flight; launch 2 adds the partials in (map, split) order.  Latency-bound:
+// eight to twelve launches of 5 to 21 us each before (104 us at 16 samples x
+// 1536 channels), two now.
+struct CbnBwdK {
+  struct {
+    const float *dgb, *W, *sigma;
+    float* dW;
+    int C, Cp, splits, kper;
+  } m[kCbnMaps];
+  int n, B, dc;
+  const float* cond;
+  float *part, *dcond;
+  int acc;
+  int off[2 * kCbnMaps + 1];   // first block of each map's dW, then of each map's dcond partials
+};
+PG_DEV int cbn_tiles(int a, int b) { return ((a + 31) >> 5) * ((b + 31) >> 5); }
 
-void cbn_linear_bwd(hipStream_t st, const float* dgb, int B, int C, int Cp, const float* cond, int dc,
-                    const float* W, const float* sigma, float* dW, float* dcond, bool accumulate, float* ws) {
-  // dW[c][j] = sum_b dgb[b][c] cond[b][j];  dcond[b][j] (+)= sum_c dgb[b][c] W[c][j] / sigma
-  gemm_small(st, C, dc, B, dgb, 1, Cp, cond, dc, 1, dW, dc, nullptr, false);
-  // K = C is long and M x N = B x dc small: split K for parallelism
-  const int splits = ws ? (int)std::min<int64_t>(kLinSplits, cdiv(C, 128)) : 1;
-  gemm_small(st, B, dc, C, dgb, Cp, 1, W, dc, 1, dcond, dc, sigma, accumulate, ws, splits);
+__global__ __launch_bounds__(256) void k_cbn_bwd(CbnBwdK g) {
+  constexpr int KC = 64;
+  __shared__ float As[32][KC + 1], Bs[KC][33];
+  int job = 0;
+  while (job + 1 < 2 * g.n && (int)blockIdx.x >= g.off[job + 1]) ++job;
+  const bool isw = job < g.n;
+  const int mi = isw ? job : job - g.n;
+  const auto& J = g.m[mi];
+  int lb = blockIdx.x - g.off[job];
+  const int M = isw ? J.C : g.B, N = g.dc, tn = (N + 31) >> 5;
+  int kb = 0, ke = isw ? g.B : J.C, slot = 0;
+  if (!isw) {
+    const int tiles = cbn_tiles(M, N), z = lb / tiles;
+    lb -= z * tiles;
+    kb = z * J.kper;
+    ke = min(ke, kb + J.kper);
+    slot = z;
+    for (int i = 0; i < mi; ++i) slot += g.m[i].splits;
+  }
+  const int i0 = (lb / tn) * 32, j0 = (lb % tn) * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const float* const Bm = isw ? g.cond : J.W;
+  float ra[KC / 8], rb[KC / 8];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int q = 0; q < KC / 8; ++q) {
+      const int kk = k0 + ty + 8 * q;
+      rb[q] = kk < ke && j0 + tx < N ? Bm[(int64_t)kk * N + j0 + tx] : 0.f;
+      if (isw) {   // A(i, k) = dgb[k][i], lanes along i
+        ra[q] = kk < ke && i0 + tx < M ? J.dgb[(int64_t)kk * J.Cp + i0 + tx] : 0.f;
+      } else {     // A(i, k) = dgb[i][k], lanes along k
+        const int r = i0 + ty + 8 * (q & 3), k = k0 + tx + 32 * (q >> 2);
+        ra[q] = k < ke && r < M ? J.dgb[(int64_t)r * J.Cp + k] : 0.f;
+      }
+    }
+  };
+  float c[4] = {0.f, 0.f, 0.f, 0.f};
+  load(kb);
+  for (int k0 = kb; k0 < ke; k0 += KC) {
+#pragma unroll
+    for (int q = 0; q < KC / 8; ++q) {
+      Bs[ty + 8 * q][tx] = rb[q];
+      if (isw) As[tx][ty + 8 * q] = ra[q];
+      else As[ty + 8 * (q & 3)][tx + 32 * (q >> 2)] = ra[q];
+    }
+    __syncthreads();
+    if (k0 + KC < ke) load(k0 + KC);
+    const int kn = min(KC, ke - k0);
+#pragma unroll 8
+    for (int kk = 0; kk < kn; ++kk) {
+      const float b = Bs[kk][tx];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) c[q] = fmaf(As[ty + 8 * q][kk], b, c[q]);
+    }
+    __syncthreads();
+  }
+  const int j = j0 + tx;
+  if (j >= N) return;
+  float* const out = isw ? J.dW : g.part + (int64_t)slot * M * N;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = i0 + ty + 8 * q;
+    if (i < M) out[(int64_t)i * N + j] = c[q];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_cbn_dcond(CbnBwdK g) {
+  const int64_t n = (int64_t)g.B * g.dc, e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= n) return;
+  float r = g.acc ? g.dcond[e] : 0.f;
+  const float* p = g.part + e;
+  for (int m = 0; m < g.n; ++m) {
+    float sum = 0.f;
+#pragma unroll 4
+    for (int z = 0; z < g.m[m].splits; ++z, p += n) sum += *p;
+    r += sum / *g.m[m].sigma;
+  }
+  g.dcond[e] = r;
+}
+
+size_t cbn_linear_bwd_ws_bytes(int B, int dc) { return align256((size_t)kCbnMaps * kLinSplits * B * dc * 4); }
+
+void cbn_linear_bwd(hipStream_t st, const CbnMap* maps, int n, int B, const float* cond, int dc, float* dcond,
+                    bool accumulate, float* ws) {
+  PG_CHECK(n >= 1 && n <= kCbnMaps, "cbn_linear_bwd: maps");
+  CbnBwdK g{};
+  g.n = n; g.B = B; g.dc = dc; g.cond = cond; g.part = ws; g.dcond = dcond; g.acc = accumulate;
+  int64_t b = 0;
+  for (int i = 0; i < n; ++i) {
+    const CbnMap& a = maps[i];
+    auto& k = g.m[i];
+    k.dgb = a.dgb; k.W = a.W; k.sigma = a.sigma; k.dW = a.dW; k.C = a.C; k.Cp = a.Cp;
+    k.kper = (int)cdiv(cdiv(a.C, std::min<int64_t>(kLinSplits, cdiv(a.C, 128))), 32) * 32;
+    k.splits = (int)cdiv(a.C, k.kper);
+    g.off[i] = (int)b;
+    b += cdiv(a.C, 32) * cdiv(dc, 32);
+  }
+  for (int i = 0; i < n; ++i) {
+    g.off[n + i] = (int)b;
+    b += cdiv(B, 32) * cdiv(dc, 32) * g.m[i].splits;
+  }
+  g.off[2 * n] = (int)b;
+  PG_CHECK(b < (1LL << 31), "cbn_linear_bwd: too large");
+  hipLaunchKernelGGL(k_cbn_bwd, dim3((unsigned)b), dim3(256), 0, st, g);
+  hipLaunchKernelGGL(k_cbn_dcond, dim3((unsigned)cdiv((int64_t)B * dc, 256)), dim3(256), 0, st, g);
   PG_LAUNCH_CHECK();
 }
 

@@ -1,6 +1,6 @@
 """Parity of the launch forms that small problems take: convolutions whose K
 loop is split over blocks, weight gradients planned in whole rounds of
-blocks.  Sizes at the edges of their tiles: partial pixel
+blocks, the conditional-BN linear maps and the sub-pixel fold.  Sizes at the edges of their tiles: partial pixel
 and channel tiles, uneven last splits, every gather and epilogue of a split
 conv.  Same oracle and bars as the block tests."""
 import pytest
@@ -53,3 +53,16 @@ def test_split_conv(kind, shape, names):
 def test_wgrad_plan(kind, shape):
     run = run_gblock if kind == "g" else run_dblock
     run(dtype=lib.BF16, seed=710, weights="gaussian", **shape)
+
+
+# Conditional-BN maps: conditioning wider than one staged chunk and not a
+# multiple of four, samples and channels past one tile, split sums over the
+# channels; the sub-pixel fold with its splits over waves (960 source pixels)
+@pytest.mark.parametrize("shape", [
+    dict(B=17, H=2, W=3, cin=264, cout=40, dc=171),
+    dict(B=33, H=1, W=2, cin=32, cout=72, dc=3),
+    dict(B=3, H=16, W=20, cin=32, cout=40, dc=148),
+])
+@pytest.mark.parametrize("dtype", [lib.BF16, lib.F32])
+def test_cbn_maps(shape, dtype):
+    run_gblock(dtype=dtype, seed=720, weights="gaussian", **shape)
