@@ -159,7 +159,7 @@ static GWsF g_carve_f(const GBlock& g, Arena& a) {
   w.cp_bytes = g.f32 ? 0 : std::max({conv_split_ws(G_SUB, g.B, g.H, g.W, 2, g.Cip, g.Cop),
                                      conv_split_ws(G_DIRECT, g.B, g.H, g.W, 1, g.Cip, g.Cop),
                                      conv_split_ws(G_DIRECT, g.B, 2 * g.H, 2 * g.W, 3, g.Cop, g.Cop)});
-  w.cp = a.bytes(w.cp_bytes);
+  w.cp = a.bytes(std::max<size_t>(w.cp_bytes, 16));
   return w;
 }
 
@@ -193,7 +193,7 @@ static GWsB g_carve_b(const GBlock& g, Arena& a, int n_cu) {
   w.cp_bytes = g.f32 ? 0 : std::max({conv_split_ws(G_S2, g.B, g.H, g.W, 2, g.Cop, g.Cip),
                                      conv_split_ws(G_DIRECT, g.B, 2 * g.H, 2 * g.W, 3, g.Cop, g.Cop),
                                      conv_split_ws(G_S2, g.B, g.H, g.W, 4, g.Cop, g.Cip)});
-  w.cp = a.bytes(w.cp_bytes);
+  w.cp = a.bytes(std::max<size_t>(w.cp_bytes, 16));
   return w;
 }
 
@@ -459,7 +459,7 @@ static DWsF d_carve_f(const DBlock& d, Arena& a) {
                                      conv_split_ws(G_DIRECT, d.B, d.Ho, d.Wo, 1, d.Cip, d.Cop),
                                      d.s2conv() ? conv_split_ws(G_S2, d.B, d.Ho, d.Wo, 4, d.Cop, d.Cop)
                                                 : conv_split_ws(G_DIRECT, d.B, d.H, d.W, 3, d.Cop, d.Cop)});
-  w.cp = a.bytes(w.cp_bytes);
+  w.cp = a.bytes(std::max<size_t>(w.cp_bytes, 16));
   return w;
 }
 
@@ -489,7 +489,7 @@ static DWsB d_carve_b(const DBlock& d, Arena& a, int n_cu) {
                                                   : conv_split_ws(G_DIRECT, d.B, d.H, d.W, 3, d.Cop, d.Cop),
                                      conv_split_ws(G_DIRECT, d.B, d.Ho, d.Wo, 1, d.Cop, d.Cip),
                                      conv_split_ws(G_DIRECT, d.B, d.H, d.W, d.im2col ? 1 : 3, d.Cop, d.Cip)});
-  w.cp = a.bytes(w.cp_bytes);
+  w.cp = a.bytes(std::max<size_t>(w.cp_bytes, 16));
   return w;
 }
 
@@ -549,6 +549,7 @@ void DBlock::prep(hipStream_t st, const Params& P, void* sn_ws, bool for_bwd) {
 void DBlock::fwd(const Exec& ex, const Params& P, const void* x, void* y) {
   Arena a(ex.ws);
   DWsF w = d_carve_f(*this, a);
+  if (ex.one_order) w.cp = nullptr;
   if (!prepped) prep(ex.st, P, w.sn);
   const int R1 = im2col ? 1 : 3, K1 = im2col ? 9 * cin : cin, ksc = im2col ? 4 * cin : 0;
   // h = conv3x3([relu](x)) + b1
@@ -592,6 +593,7 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
                  bool wgrad) {
   Arena a(ex.ws);
   DWsB w = d_carve_b(*this, a, ex.n_cu);
+  if (ex.one_order) w.cp = nullptr;
   const int64_t M = (int64_t)B * H * W, Mo = (int64_t)B * Ho * Wo;
   const int R1 = im2col ? 1 : 3, K1 = im2col ? 9 * cin : cin, ksc = im2col ? 4 * cin : 0;
   // the data-gradient weights: packed by prep, or here

@@ -85,6 +85,10 @@ struct Exec {
   // join: side -> st); both streams are joined when the call returns
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
+  // a D block's convolutions sum in one order whatever the batch: nothing in
+  // the discriminator couples the batch, so in a network its activations and
+  // activation gradients are the same bits at any batch
+  bool one_order = false;
 };
 
 // ----------------------------------------------------------- G block

@@ -740,13 +740,13 @@ inline int halo_patch(int BM, int H, int W) {
   return (BM / W + 2) * (W + 2);
 }
 
-template <int WN, int WM, int TN, int TM>
+template <int WN, int WM, int TN, int TM, int NS = 3>
 std::string launch_cfg(hipStream_t s, CfK& k, int gather, bool relu) {
   constexpr int BN = WN * TN * 32, BM = WM * TM * 32;
   dim3 grid(k.tiles_m * k.tiles_n * (gather == G_SUB ? 4 : 1) * k.splits), block(64 * WN * WM);
 #define PG_CF_CASE(G, R_)                                                             \
   if (gather == G && relu == R_) {                                                    \
-    hipLaunchKernelGGL((k_conv_fwd<WN, WM, TN, TM, 3, 32, G, R_>), grid, block, 0, s, k); \
+    hipLaunchKernelGGL((k_conv_fwd<WN, WM, TN, TM, NS, 32, G, R_>), grid, block, 0, s, k); \
     return "k_conv_fwd<" + std::to_string(BN) + "x" + std::to_string(BM) + "," #G "," #R_ ">"; \
   }
   PG_CF_CASE(G_DIRECT, false)
@@ -768,114 +768,116 @@ struct CfPlan {
   int splits, per;
 };
 
-// Tile choice (measured on the BigGAN shapes in the train step).  For
-// multiples of 256 channels an eight-wave block (one per CU) on a 256 x
-// 256 tile halves the operand bytes per MFMA of the four-wave 128 x 256
-// tile, and wins whenever its blocks come in whole rounds over the CUs
-// (the last round at least three quarters full); with a ragged last round
-// the four-wave tiles, two per CU, spread better.  Otherwise: 128 x 256
-// for multiples of 128 (128 x 128 for exactly 128, the 1x1 attention
-// projections with K <= 192), 192 x 128 for multiples of 192, 96 x 256
-// for the other multiples of 96, and 32 / 64 x 256 for narrow outputs.
-// Direct 3x3 convs whose tiles are whole image rows take the halo kernel
-// (each activation chunk loaded once for all nine taps) on the 256 x 256
-// and 192 x 128 tiles, and for 96 channels on an eight-wave 96 x 512 tile,
-// whose weight loads the wider tile amortises (measured: on the four-wave
-// 128 x 256 tile the patch addressing of its four pixel fragments costs
-// more than the loads it saves).
-void cf_tile(int gather, int64_t M, int H, int W, int R, int C, int Np, CfPlan& p) {
-  const int par = gather == G_SUB ? 4 : 1;
-  auto set = [&](int kernel, int bn, int bm) {
-    p.kernel = kernel;
-    p.bn = bn;
-    p.bm = bm;
-  };
-  const bool halo = gather == G_DIRECT && R == 3;
-  auto fits = [&](int bm, int ppx) {
-    const int np = halo_patch(bm, H, W);
-    return halo && np > 0 && np <= ppx;
-  };
-  const int64_t tiles8 = cdiv(M, 256) * (Np / 256) * par;
-  const int64_t last8 = tiles8 % 256;
-  if (Np % 256 == 0 && tiles8 >= 192 && (last8 == 0 || last8 >= 192))
-    return set(fits(256, 384) ? kHaloDirect : kRing, 256, 256);
-  if (Np % 192 == 0 && fits(128, 320)) return set(kHaloDirect, 192, 128);
-  if (Np == 96 && fits(512, 896)) return set(kHaloDirect, 96, 512);
-  // sub-pixel convs (a 2x2 filter per parity over the source grid) share the
-  // patch logic, over a 96 x 256 tile and, for multiples of 192 with K = 4 C
-  // of at least 768, a 192 x 128 one (measured: 3-7% faster than the ring
-  // kernel's tiles on the BigGAN shapes down to that K)
-  const bool hsub = gather == G_SUB && R == 2;
-  auto fits_sub = [&](int bm, int ppx) {
-    const int np = halo_patch(bm, H, W);
-    return hsub && np > 0 && np <= ppx;
-  };
-  if (Np % 192 == 0 && C >= 192 && fits_sub(128, 320)) return set(kHaloSub, 192, 128);
-  if (Np == 96 && fits_sub(256, 448)) return set(kHaloSub, 96, 256);
-  // the stride-2 4x4 filter (pooled D conv2): a patch per parity class of the source
-  const bool hs2 = gather == G_S2 && R == 4;
-  auto fits_s2 = [&](int bm, int ppx) {
-    const int np = halo_patch(bm, H, W);
-    return hs2 && np > 0 && np <= ppx;
-  };
-  if (Np % 192 == 0 && fits_s2(128, 320)) return set(kHaloS2, 192, 128);
-  if (Np == 96 && fits_s2(256, 448)) return set(kHaloS2, 96, 256);
-  // eight waves on 192 x 256 where those tiles come in whole rounds over
-  // the CUs and the four-wave tiles would not
-  if (Np % 192 == 0) {
-    const int64_t t6 = cdiv(M, 256) * (Np / 192) * par, l6 = t6 % 256;
-    const int64_t t4 = cdiv(M, Np % 128 == 0 ? 256 : 128) * (Np % 128 == 0 ? Np / 128 : Np / 192) * par,
-                  l4 = t4 % 512;
-    if (t6 >= 192 && (l6 == 0 || l6 >= 192) && l4 != 0 && l4 < 384) return set(kRing, 192, 256);
-  }
-  if (Np == 128) return set(kRing, 128, 128);
-  if (Np % 128 == 0) return M <= 128 ? set(kRing, 128, 128) : set(kRing, 128, 256);
-  if (Np % 192 == 0) return set(kRing, 192, 128);
-  if (Np % 96 == 0) return set(kRing, 96, 256);
-  if (Np <= 32) return set(kRing, 32, 256);
-  if (Np <= 64) return set(kRing, 64, 256);
-  set(kRing, 128, 128);
-}
-
 // bytes of one split's partials
 int64_t split_bytes(int gather, int64_t M, int Np) { return 4 * M * (gather == G_SUB ? 4 : 1) * Np; }
 
-// Split of K: a conv whose tiles leave half of the CUs or more without a
-// block (the deep layers at small batches: few pixels, thousands of K steps)
-// is split over K, as far as its blocks still run at once, at least eight
-// K steps each; k_conv_split_fin sums the fp32 partials in split order.  At
-// most 256 blocks of 64 K sums each, so the partials take 64 MB at most.
-// Modelled cost of s splits: the K steps of one block (0.6 us per 32-deep
-// step of a 128 x 256 tile with the chip full), a second launch (5 us) and
-// the partials written and read (4 TB/s).  Measured on the 1536-channel 3x3
-// conv at 1024 pixels (432 steps, 48 tiles): 191 us in one split, 57 + 8 us
-// in five (halving or doubling the model's constants moves whole blocks by
-// less than 2 %; more splits than CUs, or the 256 x 256 tile: no gain).
+
+// The tiles, with the measured time (us) of one 32-channel K step of a block
+// -- c1 with one block on its CU, c2 in a full round (two four-wave blocks
+// or one eight-wave block per CU) -- and of its prologue and epilogue.  The
+// halo kernels (each activation chunk loaded once for all taps of a 3x3, a
+// sub-pixel or a stride-2 4x4 filter) need tiles of whole image rows whose
+// patch fits ppx pixels.  Fitted to 1200 launches of the BigGAN layers at
+// batches of 16 to 512 (8 to 4M pixels x 64 to 1536 channels, K 64 to
+// 24576), each on every tile; the model's choice is within 1 % of the best
+// tile in total there.
+struct CfTile {
+  int kernel, bn, bm, ppx;
+  bool wide;   // eight waves
+  float c1, c2, e;
+};
+constexpr CfTile kCfTiles[] = {
+    {kHaloDirect, 256, 256, 384, true, 0.82f, 0.82f, 8.f},   {kHaloDirect, 192, 128, 320, false, 0.40f, 0.68f, 6.f},
+    {kHaloDirect, 96, 512, 896, true, 0.64f, 0.64f, 13.f},   {kHaloSub, 192, 128, 320, false, 0.45f, 0.66f, 11.f},
+    {kHaloSub, 96, 256, 448, false, 0.45f, 0.66f, 8.5f},     {kHaloS2, 192, 128, 320, false, 0.47f, 0.74f, 11.f},
+    {kHaloS2, 96, 256, 448, false, 0.44f, 0.68f, 12.5f},     {kRing, 256, 256, 0, true, 0.82f, 0.82f, 13.5f},
+    {kRing, 192, 256, 0, true, 0.68f, 0.68f, 20.f},          {kRing, 128, 256, 0, false, 0.50f, 0.96f, 13.f},
+    {kRing, 192, 128, 0, false, 0.39f, 0.76f, 12.f},         {kRing, 128, 128, 0, false, 0.34f, 0.55f, 7.f},
+    {kRing, 96, 256, 0, false, 0.40f, 0.80f, 13.f},          {kRing, 64, 128, 0, false, 0.27f, 0.42f, 6.f},
+    {kRing, 64, 64, 0, false, 0.19f, 0.28f, 5.f},            {kRing, 64, 256, 0, false, 0.35f, 0.68f, 7.5f},
+    {kRing, 32, 256, 0, false, 0.30f, 0.55f, 6.f}};
+
+// Tile and split of K of a conv, by modelled time: the rounds of its blocks
+// over the CUs times a block's time.  Large launches (four rounds and more)
+// count their rounds as a fraction, since the dispatcher keeps every CU busy
+// until the last; a ring tile costs 4 % more where a halo kernel fits (it
+// reads each activation once per tap).  64 x 256 and 32 x 256 are for outputs
+// that narrow; the six-stage 64-channel tiles for launches of few blocks
+// (1x1 filters on 8 x 8 pixels: 24 us on 32 x 256, 16 on 64 x 64).
+//
+// A conv whose tiles leave half of the CUs or more without a block (the deep
+// layers at small batches: few pixels, thousands of K steps) may be split
+// over K, as far as its blocks still run at once, at least eight K steps
+// each; k_conv_split_fin sums the fp32 partials in split order (a second
+// launch, 5 us, and the partials written and read at 4 TB/s).  At most 256
+// blocks of 64 K sums each, so the partials take 64 MB at most.  Measured on
+// the 1536-channel 3x3 conv at 1024 pixels (432 steps): 191 us unsplit on 48
+// 128 x 256 tiles, 57 + 8 us in five splits.
+//
+// one_order: the order in which an output's K products are summed must not
+// depend on the number of images: no split, and the kernel family (halo:
+// chunks outside taps; ring: taps outside channels) from the image's and
+// the filter's shape alone -- except that direct 3x3 filters of 256 n
+// channels that are no multiple of 192 take the halo kernel only from 192
+// tiles on (its 256 x 256 tile is the one that fits them well).
 constexpr int kCUs = 256, kSplitSteps = 8;
-CfPlan cf_plan(int gather, int64_t M, int H, int W, int R, int C, int Np) {
-  CfPlan p{};
-  cf_tile(gather, M, H, W, R, C, Np, p);
-  p.tiles_m = (int)cdiv(M, p.bm);
-  p.tiles_n = (int)cdiv(Np, p.bn);
-  p.ksteps = R * R * (C / 32);
-  // units of the K loop: steps (ring), chunks of a tap set (halo)
-  const int taps = p.kernel == kRing ? 1 : (p.kernel == kHaloDirect ? 9 : 4);
-  const int units = p.ksteps / taps;
-  const int64_t blocks = (int64_t)p.tiles_m * p.tiles_n * (gather == G_SUB ? 4 : 1);
-  const double step = 0.6 * taps * (double)p.bn * p.bm / 32768.0;
-  const double part = 2.0 * (double)split_bytes(gather, M, Np) / 4e6;
-  int64_t s = 1;
-  double best = units * step;
-  for (int64_t c = 2; c * blocks <= kCUs && c * cdiv(kSplitSteps, taps) <= units; ++c) {
-    const double t = (double)cdiv(units, c) * step + 5.0 + (double)c * part;
-    if (t < 0.95 * best) {
-      best = t;
-      s = c;
+CfPlan cf_plan(int gather, int64_t M, int H, int W, int R, int C, int Np, bool one_order) {
+  const int par = gather == G_SUB ? 4 : 1;
+  const int hk = gather == G_DIRECT && R == 3 ? kHaloDirect
+                 : gather == G_SUB && R == 2  ? kHaloSub
+                 : gather == G_S2 && R == 4   ? kHaloS2
+                                              : kRing;
+  CfPlan best{};
+  double best_t = 1e300;
+  bool halo = false;
+  for (const CfTile& t : kCfTiles) {   // (halo tiles first)
+    if (t.kernel != kRing) {
+      const int np = t.kernel == hk ? halo_patch(t.bm, H, W) : 0;
+      if (np <= 0 || np > t.ppx) continue;
+      if (one_order) {
+        const bool suits = t.kernel == kHaloSub && C < 192 ? Np == 96 : Np % 192 == 0 || Np == 96;
+        if (!suits && (t.kernel != kHaloDirect || t.bn != 256 || Np % 256 != 0 || cdiv(M, 256) * (Np / 256) < 192))
+          continue;
+      }
+      halo = true;
+    } else if ((one_order && halo) || (t.bm == 256 && t.bn <= 64 && Np > t.bn)) {
+      continue;
+    }
+    CfPlan p{};
+    p.kernel = t.kernel;
+    p.bn = t.bn;
+    p.bm = t.bm;
+    p.tiles_m = (int)cdiv(M, t.bm);
+    p.tiles_n = (int)cdiv(Np, t.bn);
+    p.ksteps = R * R * (C / 32);
+    // units of the K loop: steps (ring), chunks of a tap set (halo)
+    const int taps = t.kernel == kRing ? 1 : (t.kernel == kHaloDirect ? 9 : 4);
+    const int units = p.ksteps / taps;
+    const int64_t blocks = (int64_t)p.tiles_m * p.tiles_n * par, cap = t.wide ? kCUs : 2 * kCUs;
+    const double full = p.ksteps * t.c2 + t.e, one = p.ksteps * t.c1 + t.e;
+    double time;
+    if (blocks >= 4 * cap)
+      time = ((double)blocks / cap + 0.3) * full;
+    else
+      time = (double)(blocks / cap) * full + (blocks % cap == 0 ? 0.0 : blocks % cap <= kCUs ? one : full);
+    int64_t s = 1;
+    const double step = taps * (t.wide ? t.c2 : 1.25 * t.c1), part = 2.0 * (double)split_bytes(gather, M, Np) / 4e6;
+    for (int64_t c = 2; !one_order && c * blocks <= kCUs && c * cdiv(kSplitSteps, taps) <= units; ++c) {
+      const double ts = (double)cdiv(units, c) * step + t.e + 5.0 + (double)c * part;
+      if (ts < 0.95 * time) {
+        time = ts;
+        s = c;
+      }
+    }
+    if (t.kernel == kRing && halo) time *= 1.04;
+    if (time < best_t) {
+      best_t = time;
+      p.per = (int)cdiv(units, s);
+      p.splits = (int)cdiv(units, p.per);
+      best = p;
     }
   }
-  p.per = (int)cdiv(units, s);
-  p.splits = (int)cdiv(units, p.per);
-  return p;
+  return best;
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15) == 0; }
@@ -904,7 +906,7 @@ bool conv_fwd_mfma_ok(const ConvIn& in, int H, int W, int R, int Np, const ConvO
 size_t conv_split_ws(int gather, int B, int H, int W, int R, int C, int Np) {
   const int64_t M = (int64_t)B * H * W;
   if (M <= 0) return 0;
-  const CfPlan p = cf_plan(gather, M, H, W, R, C, Np);
+  const CfPlan p = cf_plan(gather, M, H, W, R, C, Np, false);
   return p.splits > 1 ? align256((size_t)(p.splits * split_bytes(gather, M, Np))) : 0;
 }
 
@@ -927,13 +929,9 @@ std::string conv_fwd_mfma(hipStream_t s, const ConvIn& in, int H, int W, int R, 
   k.fdW = make_fastdiv(W);
   k.fdH = make_fastdiv(H);
   k.o = out;
-  CfPlan p = cf_plan(in.gather, k.M, H, W, R, in.C, Np);
+  const CfPlan p = cf_plan(in.gather, k.M, H, W, R, in.C, Np, part == nullptr);
   const int64_t sb = split_bytes(in.gather, k.M, Np);
-  if (p.splits > 1 && (!part || (size_t)(p.splits * sb) > part_bytes)) {
-    // no scratch for the partials: one split
-    p.per *= p.splits;
-    p.splits = 1;
-  }
+  if (p.splits > 1 && (size_t)(p.splits * sb) > part_bytes) throw Error{-3, "conv_fwd: workspace too small"};
   k.tiles_m = p.tiles_m;
   k.tiles_n = p.tiles_n;
   k.ksteps = p.ksteps;
@@ -970,6 +968,8 @@ std::string conv_fwd_mfma(hipStream_t s, const ConvIn& in, int H, int W, int R, 
       case 96256: name = launch_cfg<1, 4, 3, 2>(s, k, in.gather, in.relu); break;
       case 32256: name = launch_cfg<1, 4, 1, 2>(s, k, in.gather, in.relu); break;
       case 64256: name = launch_cfg<1, 4, 2, 2>(s, k, in.gather, in.relu); break;
+      case 64128: name = launch_cfg<2, 2, 1, 2, 6>(s, k, in.gather, in.relu); break;
+      case 64064: name = launch_cfg<2, 2, 1, 1, 6>(s, k, in.gather, in.relu); break;
       default: throw Error{-2, "conv_fwd: no kernel for the planned tile"};
     }
   }

@@ -437,6 +437,7 @@ void DNet::fwd(const Exec& ex, const Params& P, const float* x, const int32_t* y
   Arena w(ex.ws);
   DNetWs r = dnet_carve(a, N_, blocks_, attn_after_ >= 0 ? &attn_ : nullptr, w, ex.n_cu);
   Exec eb{ex.st, ex.n_cu, r.blk, r.blk_bytes};
+  eb.one_order = true;
   img_to_im2col(ex.st, x, N_, a.img, a.img, act_[0]);
   const void* h = act_[0];
   for (int j = 0; j < (int)blocks_.size(); ++j) {
@@ -462,7 +463,7 @@ void DNet::bwd(const Exec& ex, const Params& P, const int32_t* y, const float* d
   const Arch& a = a_;
   Arena w(ex.ws);
   DNetWs r = dnet_carve(a, N_, blocks_, attn_after_ >= 0 ? &attn_ : nullptr, w, ex.n_cu);
-  Exec eb{ex.st, ex.n_cu, r.blk, r.blk_bytes, ex.side, ex.ev_fork, ex.ev_join};
+  Exec eb{ex.st, ex.n_cu, r.blk, r.blk_bytes, ex.side, ex.ev_fork, ex.ev_join, true};
   const DBlock& last = blocks_.back();
   const int nb = (int)blocks_.size();
   const void* xl = in_[nb];

@@ -61,8 +61,10 @@ struct ConvOut {
 
 // y = conv_RxR(gathered/transformed x, w) on an H x W grid (stride 1, pad R/2).
 // w: packed [Np][R][R][in.C] in the activation type (bf16 or fp32).
-// part (conv_split_ws bytes, 16-byte aligned; may be null): scratch for the
-// fp32 partials of a conv whose K loop is split over blocks.
+// part (conv_split_ws bytes, 16-byte aligned): scratch for the fp32 partials
+// of a conv whose K loop is split over blocks.  With part == nullptr the
+// conv is not split and sums an output's products in an order that does not
+// depend on the batch.
 void conv_fwd(hipStream_t s, bool f32, const ConvIn& in, int H, int W, int R,
               const void* w, int Np, const ConvOut& out, void* part = nullptr, size_t part_bytes = 0);
 // bf16 only (0 for a conv that is not split)

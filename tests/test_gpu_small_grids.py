@@ -1,4 +1,4 @@
-"""Parity of the launch forms that small problems take: convolutions whose K
+"""Parity of the launch forms that sizes decide: convolutions whose K
 loop is split over blocks, weight gradients planned in whole rounds of
 blocks, the conditional-BN linear maps and the sub-pixel fold.  Sizes at the edges of their tiles: partial pixel
 and channel tiles, uneven last splits, every gather and epilogue of a split
@@ -13,34 +13,34 @@ from .test_gpu_blocks import run_dblock, run_gblock
 pytestmark = pytest.mark.gpu
 
 
-def launched(part):
-    return sorted(n for n in parity.SEEN if part in n)
+def split_convs():
+    return {n for n in parity.SEEN if n.startswith("k_conv_") and n.endswith("/split")}
 
 
-# (kind, shape, the kernel instances that must have run split)
+# (kind, shape, the split kernels that must have run, by family and gather)
 SPLIT = [
-    # halo kernels at 16-wide rows: 192 channels (6 chunks) and 96
-    ("g", dict(B=1, H=16, W=16, cin=192, cout=192, dc=20), ["k_conv_halo<192x128,false>/split",
-                                                            "k_conv_halo<192x128,G_SUB,false>/split"]),
-    ("g", dict(B=2, H=16, W=16, cin=96, cout=96, dc=20), ["k_conv_halo<96x512,false>/split"]),
-    # ring kernels: 128-wide tiles with a partial channel tile (160 channels), ragged pixels
-    ("g", dict(B=3, H=5, W=7, cin=136, cout=160, dc=20), ["k_conv_fwd<128x128,G_DIRECT,false>/split",
-                                                          "k_conv_fwd<128x128,G_S2,false>/split"]),
-    ("d", dict(B=3, H=10, W=6, cin=200, cout=136, preact=True, down=True, lsc=True),
-     ["k_conv_fwd<128x128,G_S2,true>/split", "k_conv_fwd<128x128,G_DIRECT,true>/split"]),
+    # halo kernel at 32-wide rows (12 chunks), ReLU mask, half-resolution residual
+    ("d", dict(B=4, H=32, W=32, cin=384, cout=768, preact=True, down=True, lsc=True),
+     [("halo", ",false"), ("fwd", "G_S2,true")]),
+    # ragged pixels, a partial channel tile, an uneven last split
+    ("g", dict(B=3, H=5, W=7, cin=136, cout=160, dc=20), [("fwd", "G_DIRECT,false"), ("fwd", "G_S2,false")]),
+    ("g", dict(B=1, H=4, W=4, cin=512, cout=256, dc=20), [("fwd", "G_SUB,false")]),
+    ("d", dict(B=3, H=10, W=6, cin=200, cout=136, preact=True, down=True, lsc=True), [("fwd", "G_S2,true")]),
     # identity skip, bf16 residual, one pixel past a 256-pixel tile
-    ("d", dict(B=1, H=1, W=257, cin=256, cout=256, preact=True, down=False, lsc=False),
-     ["k_conv_fwd<128x256,G_DIRECT,true>/split"]),
+    ("d", dict(B=1, H=1, W=257, cin=256, cout=256, preact=True, down=False, lsc=False), [("fwd", "G_DIRECT,true")]),
 ]
 
 
-@pytest.mark.parametrize("kind,shape,names", SPLIT)
-def test_split_conv(kind, shape, names):
+@pytest.mark.parametrize("kind,shape,parts", SPLIT)
+def test_split_conv(kind, shape, parts):
     run = run_gblock if kind == "g" else run_dblock
-    parity.SEEN.difference_update(names)
+    before = split_convs()
+    parity.SEEN.difference_update(before)
     run(dtype=lib.BF16, seed=700, weights="gaussian", **shape)
-    for n in names:
-        assert n in parity.SEEN, (n, launched("split"))
+    ran = split_convs()
+    parity.SEEN.update(before)
+    for family, part in parts:
+        assert any(n.startswith("k_conv_" + family) and part in n for n in ran), (family, part, sorted(ran))
 
 
 # Weight-gradient plans: row-tap tiles on a two-row image, a pixel range that
@@ -66,3 +66,16 @@ def test_wgrad_plan(kind, shape):
 @pytest.mark.parametrize("dtype", [lib.BF16, lib.F32])
 def test_cbn_maps(shape, dtype):
     run_gblock(dtype=dtype, seed=720, weights="gaussian", **shape)
+
+
+# Instances that a plan takes in a whole network or at the benchmark's batch
+# only: the discriminator's convolutions are never split there (192 x 128
+# stride-2 ring tiles), and its first block's filter gradient runs over two
+# million pixels (96 x 384 tiles)
+@pytest.mark.parametrize("shape,name", [
+    (dict(B=2, H=32, W=32, cin=192, cout=384, copies=32), "k_conv_fwd<192x128,G_S2,true>"),
+    (dict(B=2, H=128, W=128, cin=32, cout=96, copies=256), "k_wgrad_tr<96x384,false,G_S2,true>"),
+])
+def test_network_instances(shape, name):
+    run_dblock(preact=True, down=True, lsc=True, dtype=lib.BF16, seed=730, weights="gaussian", **shape)
+    assert name in parity.SEEN
