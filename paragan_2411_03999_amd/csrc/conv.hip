@@ -13,7 +13,7 @@
 //
 // bf16 path: v_mfma_f32_32x32x16_bf16, fp32 accumulation, 4 waves per
 // 256-thread block, double-buffered LDS, one barrier per K step.
-// fp32 path: a plain LDS-tiled SIMT GEMM (used by the fp32 block config and
+// fp32 path: the fp32 matrix cores (used by the fp32 block config and
 // tests; the bf16 path is the performance path).
 #include <cmath>
 
@@ -398,6 +398,102 @@ __global__ __launch_bounds__(256) void k_conv_f32mfma(ConvK k) {
   }
 }
 
+// The same product for grids that leave CUs idle (the fp32 configuration's
+// own sizes: 1024 pixels x 64 channels is 16 tiles of 64 x 64, each 36 K
+// steps of load, barrier, eight products, barrier: 39 us).  A block takes a
+// 32 x 32 tile and its four waves a quarter of the K steps each, with the
+// operands straight from memory in registers: a lane's four consecutive
+// channels of its row feed four products (lanes below 32 the channels 8 q ..
+// 8 q + 3, the others 8 q + 4 .. 8 q + 7, of both operands alike), and the
+// next 32 channels' loads are in flight during this step's 16 products.  The
+// waves' sums combine in wave order through LDS.  1024 pixels x 64 x 576:
+// 39 -> 11 us.
+template <int GATHER, bool RELU>
+__global__ __launch_bounds__(256) void k_conv_f32r(ConvK k) {
+  __shared__ float red[4][16][64];
+  const AOp& a = k.a;
+  const int tmi = blockIdx.x / k.tiles_n, tni = blockIdx.x - tmi * k.tiles_n;
+  const int64_t m = (int64_t)tmi * 32 + (threadIdx.x & 31);
+  const int n0 = tni * 32;
+  const int lane = threadIdx.x & 63, l32 = lane & 31, kh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool mv = m < a.M, nv = n0 + l32 < k.Np;
+  int b, oh, ow;
+  decode_m(mv ? m : 0, a.H, a.W, k.o.pool, b, oh, ow);
+  const float* X = (const float*)a.x;
+  const int RR = a.R * a.R, cch = a.C / 32;
+  const float* wrow = (const float*)k.w + (int64_t)(nv ? n0 + l32 : 0) * RR * a.C + 4 * kh;
+  const int per = (RR * cch + 3) >> 2;
+  const int s0 = wave * per, s1 = min(s0 + per, RR * cch);
+  float4 wv[2][4], xv[2][4];
+  auto load = [&](int st, float4 (&w4)[4], float4 (&x4)[4]) {
+    const int tap = st / cch, c0 = (st - tap * cch) * 32 + 4 * kh;
+    const int r = tap / a.R, s = tap - r * a.R;
+    const int ih = oh + r - a.pad, iw = ow + s - a.pad;
+    const bool ok = mv && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
+    int64_t off[4] = {0, 0, 0, 0};
+    const int ns = src_offsets<GATHER>(a, b, ok ? ih : 0, ok ? iw : 0, c0, off);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      w4[q] = nv ? *reinterpret_cast<const float4*>(wrow + (int64_t)tap * a.C + c0 - 4 * kh + 8 * q)
+                 : make_float4(0.f, 0.f, 0.f, 0.f);
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (ok) {
+#pragma unroll
+        for (int d = 0; d < 4; ++d)
+          if (d < ns) {
+            const float4 t = *reinterpret_cast<const float4*>(X + off[d] + 8 * q);
+            if (d == 0) v = t;
+            else { v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w; }
+          }
+      }
+      x4[q] = v;
+    }
+  };
+  auto xf = [&](float v) {
+    v *= a.gscale;
+    return RELU ? fmaxf(v, 0.f) : v;
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+  auto step = [&](const float4 (&w4)[4], const float4 (&x4)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[q].x, xf(x4[q].x), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[q].y, xf(x4[q].y), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[q].z, xf(x4[q].z), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[q].w, xf(x4[q].w), acc, 0, 0, 0);
+    }
+  };
+  if (s0 < s1) load(s0, wv[0], xv[0]);
+  for (int st = s0; st < s1; st += 2) {
+    if (st + 1 < s1) load(st + 1, wv[1], xv[1]);
+    step(wv[0], xv[0]);
+    if (st + 1 >= s1) break;
+    if (st + 2 < s1) load(st + 2, wv[0], xv[0]);
+    step(wv[1], xv[1]);
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
+  __syncthreads();
+  const float accs = (k.o.acc_scale ? *k.o.acc_scale : 1.f) * k.o.acc_mul / (k.o.acc_div ? *k.o.acc_div : 1.f);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = 4 * wave + i;
+    float v = (red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane]);
+    const int col = n0 + i + 8 * wave + 4 * kh;
+    const float bias = (k.o.bias && col < k.o.n_real) ? k.o.bias[col] : 0.f;
+    if (!k.o.pool) {
+      if (col < k.o.yC && mv) epi_store(k, m, col, v * accs + bias, a.H, a.W);
+    } else {   // (as in k_conv_f32mfma)
+      v += __shfl_xor(v, 1);
+      v += __shfl_xor(v, 2);
+      if ((lane & 3) == 0 && col < k.o.yC && mv) epi_store(k, m >> 2, col, 0.25f * v * accs + bias, a.H, a.W);
+    }
+  }
+}
+
 // --------------------------------------------------------------- launcher
 static std::string kname(const char* base, std::initializer_list<int> args);
 
@@ -452,6 +548,33 @@ void conv_fwd(hipStream_t s, bool f32, const ConvIn& in, int H, int W, int R,
     k.ksteps = R * R * k.cchunks;
     k.tiles_m = (int)cdiv(k.a.M, 64);
     k.tiles_n = (int)cdiv(Np, 64);
+    // 32 x 32 tiles with K over the waves up to 2048 tiles of 64 x 64 (fwd+bwd
+    // of a 96-channel block, 1024 tiles: 920 -> 852 us; of a 128-channel one,
+    // 4096 tiles, whose operands are better shared through LDS: 3576 -> 3905)
+    if (!aff && (int64_t)k.tiles_m * k.tiles_n < 2048) {
+      const std::string name = kname("k_conv_f32r", {in.gather, (int)in.relu});
+      k.tiles_m = (int)cdiv(k.a.M, 32);
+      k.tiles_n = (int)cdiv(Np, 32);
+      dim3 grid(k.tiles_m * k.tiles_n), block(256);
+      bool done = true;
+      if (in.gather == G_DIRECT && !in.relu)
+        hipLaunchKernelGGL((k_conv_f32r<G_DIRECT, false>), grid, block, 0, s, k);
+      else if (in.gather == G_DIRECT)
+        hipLaunchKernelGGL((k_conv_f32r<G_DIRECT, true>), grid, block, 0, s, k);
+      else if (in.gather == G_UP2 && !in.relu)
+        hipLaunchKernelGGL((k_conv_f32r<G_UP2, false>), grid, block, 0, s, k);
+      else if (in.gather == G_POOL2 && !in.relu)
+        hipLaunchKernelGGL((k_conv_f32r<G_POOL2, false>), grid, block, 0, s, k);
+      else
+        done = false;
+      if (done) {
+        PG_LAUNCH_CHECK();
+        prof.done(name, flops);
+        return;
+      }
+      k.tiles_m = (int)cdiv(k.a.M, 64);
+      k.tiles_n = (int)cdiv(Np, 64);
+    }
     dim3 grid(k.tiles_m * k.tiles_n), block(256);
 #define PG_F32_CASE(G, A_, R_)                                                     \
   if (in.gather == G && aff == A_ && (bool)in.relu == R_) {                         \
@@ -793,7 +916,9 @@ static void wgrad_plan(bool f32, int64_t M, int R, int Cin, int Np, int n_cu,
   const int64_t tiles = (int64_t)tiles_n * tiles_k;
   const int64_t want = 4LL * n_cu;             // ~2 waves of 2 blocks per CU
   int64_t sp = cdiv(want, tiles);
-  const int64_t minrows = f32 ? 256 : 1024;    // keep each split's K-loop long
+  // keep each split's K-loop long (fp32 over few pixels: the loop is latency-
+  // bound, 1.2 us per 16 pixels; 1024 pixels in splits of 256: 20 us, of 128: 11)
+  const int64_t minrows = f32 ? (M <= 4096 ? 128 : 256) : 1024;
   sp = std::min<int64_t>(sp, std::max<int64_t>(1, M / minrows));
   // cap the partial buffer at 512 MB
   const int64_t cap = (512LL << 20) / (4 * (int64_t)Np * Kdim);

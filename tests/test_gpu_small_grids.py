@@ -79,3 +79,16 @@ def test_cbn_maps(shape, dtype):
 def test_network_instances(shape, name):
     run_dblock(preact=True, down=True, lsc=True, dtype=lib.BF16, seed=730, weights="gaussian", **shape)
     assert name in parity.SEEN
+
+
+# fp32 convolutions in 32 x 32 tiles, the K steps over four waves: fewer steps
+# than waves (one 1x1 step), pixels past a tile, every gather and epilogue
+@pytest.mark.parametrize("kind,shape", [
+    ("g", dict(B=1, H=3, W=3, cin=20, cout=36, dc=9)),
+    ("g", dict(B=2, H=5, W=7, cin=72, cout=40, dc=9)),
+    ("d", dict(B=3, H=6, W=10, cin=20, cout=68, preact=True, down=True, lsc=True)),
+    ("d", dict(B=2, H=5, W=3, cin=40, cout=40, preact=True, down=False, lsc=False)),
+])
+def test_f32_small(kind, shape):
+    run = run_gblock if kind == "g" else run_dblock
+    run(dtype=lib.F32, seed=740, weights="gaussian", **shape)
