@@ -330,13 +330,12 @@ void GBlock::bwd(const Exec& ex, const Params& P, const void* x, const float* co
   ConvIn ia2;
   ia2.x = a2; ia2.B = B; ia2.Hx = H2; ia2.Wx = W2; ia2.C = Cop;
   conv_wgrad(sw, f32, gdy, ia2, H2, W2, 3, Cop, w.dwp2, w.wg, w.wg_bytes, ex.n_cu);
-  colsum(sw, f32, dy, M2, cout, Cop, 1.f, P.gr("conv2.b"), w.cs);
-  // skip: dWsc at full resolution against up2(x); dbsc = db2
+  // both biases add to the block output: their gradients are the same column sum of dy
+  colsum(sw, f32, dy, M2, cout, Cop, 1.f, P.gr("conv2.b"), w.cs, P.gr("sc.b"));
+  // skip: dWsc at full resolution against up2(x)
   ConvIn ax;
   ax.x = x; ax.B = B; ax.Hx = H; ax.Wx = W; ax.C = Cip; ax.gather = G_UP2;
   conv_wgrad(sw, f32, gdy, ax, H2, W2, 1, Cop, w.dwpsc, w.wg, w.wg_bytes, ex.n_cu);
-  // both biases add to the block output: their gradients are the same column sum of dy
-  PG_HIP(hipMemcpyAsync(P.gr("sc.b"), P.gr("conv2.b"), (size_t)cout * 4, hipMemcpyDeviceToDevice, sw));
   // dx_skip = Wsc^T sum2x2(dy)   (low resolution, fp32); in bf16 one
   // stride-2 2x2 conv with Wsc^T on every tap
   ConvIn dsp;
@@ -626,7 +625,8 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
     } else {
       conv_wgrad(sw, f32, g2, a2, H, W, 3, Cop, w.dwp2, w.wg, w.wg_bytes, ex.n_cu);
     }
-    colsum(sw, f32, dy, Mo, cout, Cop, 1.f, P.gr("conv2.b"), w.cs);
+    // both biases add to the block output (after the pool): the same column sum of dy
+    colsum(sw, f32, dy, Mo, cout, Cop, 1.f, P.gr("conv2.b"), w.cs, lsc ? P.gr("sc.b") : nullptr);
   }
   // dh = (conv2^T dc2) * [h > 0]
   ConvIn d2;
@@ -659,11 +659,7 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
     ConvIn as;
     as.x = x; as.B = B; as.Hx = H; as.Wx = W; as.C = Cip; as.c_real = cin;
     if (down) { as.x = xp; as.Hx = Ho; as.Wx = Wo; }
-    if (wgrad) {
-      conv_wgrad(sw, f32, gs, as, Ho, Wo, 1, Cop, w.dwpsc, w.wg, w.wg_bytes, ex.n_cu);
-      // both biases add to the block output (after the pool): the same column sum of dy
-      PG_HIP(hipMemcpyAsync(P.gr("sc.b"), P.gr("conv2.b"), (size_t)cout * 4, hipMemcpyDeviceToDevice, sw));
-    }
+    if (wgrad) conv_wgrad(sw, f32, gs, as, Ho, Wo, 1, Cop, w.dwpsc, w.wg, w.wg_bytes, ex.n_cu);
     if (dx) {
       ConvIn ds;
       ds.x = dy; ds.B = B; ds.Hx = Ho; ds.Wx = Wo; ds.C = Cop;

@@ -827,7 +827,13 @@ void sn_bwd(hipStream_t st, const float* dwp, const float* W, const float* u, co
 // them: enough blocks to fill the chip, few partials for level 2.  Statistics use shifted sums per thread (shift = the thread's
 // first value, so the sums stay well conditioned) and Chan's parallel
 // variance formula for every merge.
-constexpr int kRowsPerThread = 32;   // minimum rows per thread
+// rows per thread: 32, down to 8 where that leaves fewer than about 512 blocks
+// (1024 rows of 64 channels: one block of 32 rows per thread, 13 us; four of
+// 8, 5 us), more where 32 would make over kMaxChunks chunks
+constexpr int kRowsPerThread = 32, kRowsMin = 8;
+inline int rows_per_thread(int64_t per_row) {   // per_row: row lanes in all, rows / P
+  return (int)std::max<int64_t>(kRowsMin, std::min<int64_t>(kRowsPerThread, cdiv(per_row, 512)));
+}
 constexpr int kMaxChunks = 1024;
 
 struct RedShape {
@@ -838,7 +844,7 @@ inline RedShape red_shape(int C, int64_t M) {
   RedShape r;
   r.CC = (int)(cpad(C) / 8);
   r.P = std::max(1, 256 / r.CC);
-  const int64_t rpt = std::max<int64_t>(kRowsPerThread, cdiv(M, (int64_t)kMaxChunks * r.P));
+  const int64_t rpt = std::max<int64_t>(rows_per_thread(cdiv(M, r.P)), cdiv(M, (int64_t)kMaxChunks * r.P));
   r.rows_blk = (int)(r.P * rpt);
   return r;
 }
@@ -937,7 +943,8 @@ __global__ __launch_bounds__(256) void k_colred(const T* x, int64_t M, int C, in
 
 // fixed-order sum of the chunk partials: 16 channels per block, 64 lane
 // groups summing every 64th chunk, then the 64 group sums in order
-__global__ __launch_bounds__(1024) void k_colsum_fin(const float* part, int nch, int C, float scale, float* out) {
+__global__ __launch_bounds__(1024) void k_colsum_fin(const float* part, int nch, int C, float scale, float* out,
+                                                     float* out2) {
   __shared__ float sp[64][16];
   const int cl = threadIdx.x & 15, grp = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + cl;
@@ -950,6 +957,7 @@ __global__ __launch_bounds__(1024) void k_colsum_fin(const float* part, int nch,
     float t = 0.f;
     for (int i = 0; i < 64; ++i) t += sp[i][cl];
     out[c] = t * scale;
+    if (out2) out2[c] = t * scale;
   }
 }
 
@@ -958,9 +966,10 @@ size_t colsum_ws_bytes(int64_t M, int C) {
 }
 
 void colsum(hipStream_t st, bool f32, const void* x, int64_t M, int C, int ldc, float scale, float* out,
-            void* ws) {
+            void* ws, float* out2) {
   if (M <= 0) {
     fill(st, out, C, 0.f);
+    if (out2) fill(st, out2, C, 0.f);
     return;
   }
   const RedShape sh = red_shape(C, M);
@@ -974,7 +983,7 @@ void colsum(hipStream_t st, bool f32, const void* x, int64_t M, int C, int ldc, 
   else
     hipLaunchKernelGGL((k_colred<bf16_t, false>), dim3(nch), dim3(256), 0, st, (const bf16_t*)x, M, C, ldc, sh,
                        part, nullptr);
-  hipLaunchKernelGGL(k_colsum_fin, dim3((unsigned)cdiv(C, 16)), dim3(1024), 0, st, part, nch, C, scale, out);
+  hipLaunchKernelGGL(k_colsum_fin, dim3((unsigned)cdiv(C, 16)), dim3(1024), 0, st, part, nch, C, scale, out, out2);
   ps.done_bytes("colsum", (double)M * C * (f32 ? 4 : 2));
   PG_LAUNCH_CHECK();
 }
@@ -1253,7 +1262,7 @@ inline BnbShape bnb_shape(int B, int HW, int C) {
   BnbShape s;
   s.CC = (int)(cpad(C) / 8);
   s.P = std::max(1, 256 / s.CC);
-  const int maxch = std::max(1, HW / (s.P * kRowsPerThread));
+  const int maxch = std::max(1, HW / (s.P * rows_per_thread(cdiv((int64_t)B * HW, s.P))));
   s.nchs = std::min(maxch, std::max(1, kMaxChunks / B));
   s.rows = (int)cdiv(HW, s.nchs);
   s.nchs = (int)cdiv(HW, s.rows);
@@ -1351,35 +1360,14 @@ __global__ __launch_bounds__(256) void k_bnb_reduce(const float* g, int g_up2, c
   }
 }
 
-// pass 2a, per (sample, channel): s1 = sum of the chunk partials of dz,
-// s2 = of dz * xhat (fixed order), written over the first chunk's slot;
-// per-sample gain / bias gradients when dg_stride != 0.
-__global__ void k_bnb_fin1(float* p1, float* p2, int nch, int B, int C, float* dgain, float* dbias,
-                           int dg_stride) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (int64_t)B * C) return;
-  const int b = (int)(i / C), c = (int)(i - (int64_t)b * C);
-  float s1 = 0.f, s2 = 0.f;
-  for (int j = 0; j < nch; ++j) {
-    const int64_t o = ((int64_t)b * nch + j) * C + c;
-    s1 += p1[o];
-    s2 += p2[o];
-  }
-  const int64_t o0 = (int64_t)b * nch * C + c;
-  p1[o0] = s1;
-  p2[o0] = s2;
-  if (dg_stride) {
-    dbias[(int64_t)b * dg_stride + c] = s1;
-    dgain[(int64_t)b * dg_stride + c] = s2;
-  }
-}
-
-// pass 2b, per channel: A = sum_b gain*s1 / N, Bc = sum_b gain*s2 / N (and the
-// plain-BN gain / bias gradients sum_b s2, sum_b s1); 16 waves stride the
-// samples, combined in order.
-__global__ __launch_bounds__(1024) void k_bnb_fin2(const float* p1, const float* p2, int nch, int B, int C,
-                                                   const float* gain, int tab_stride, int64_t N, float* dgain,
-                                                   float* dbias, float* A, float* Bc, int dg_stride) {
+// pass 2, per channel: for each sample s1 = sum of the chunk partials of dz
+// and s2 = of dz * xhat, in chunk order (the per-sample gain / bias gradients
+// when dg_stride != 0), then A = sum_b gain*s1 / N, Bc = sum_b gain*s2 / N
+// (and the plain-BN gain / bias gradients sum_b s2, sum_b s1); 16 waves
+// stride the samples, combined in order.
+__global__ __launch_bounds__(1024) void k_bnb_fin(const float* __restrict__ p1, const float* __restrict__ p2, int nch,
+                                                  int B, int C, const float* gain, int tab_stride, int64_t N,
+                                                  float* dgain, float* dbias, float* A, float* Bc, int dg_stride) {
   __shared__ float sh[4][16][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + lane;
@@ -1387,8 +1375,17 @@ __global__ __launch_bounds__(1024) void k_bnb_fin2(const float* p1, const float*
   if (c < C)
     for (int b = wv; b < B; b += 16) {
       const int64_t o0 = (int64_t)b * nch * C + c;
-      const float s1 = p1[o0], s2 = p2[o0];
       const float ga = gain[(int64_t)b * tab_stride + c];
+      float s1 = 0.f, s2 = 0.f;
+#pragma unroll 8
+      for (int j = 0; j < nch; ++j) {
+        s1 += p1[o0 + (int64_t)j * C];
+        s2 += p2[o0 + (int64_t)j * C];
+      }
+      if (dg_stride) {
+        dbias[(int64_t)b * dg_stride + c] = s1;
+        dgain[(int64_t)b * dg_stride + c] = s2;
+      }
       a = fmaf(ga, s1, a);
       bb = fmaf(ga, s2, bb);
       ab += s1;
@@ -1488,10 +1485,8 @@ void bn_bwd(hipStream_t st, bool f32, const float* g, bool g_up2, const void* x,
   else
     hipLaunchKernelGGL(k_bnb_reduce<bf16_t>, g1, dim3(256), 0, st, g, (int)g_up2, (const bf16_t*)x, HW, H, W, fdW,
                        C, Cp, mean, rstd, gain, bias, tab_stride, sh, p1, p2);
-  hipLaunchKernelGGL(k_bnb_fin1, dim3((unsigned)cdiv((int64_t)B * C, 256)), dim3(256), 0, st, p1, p2, nch, B, C,
-                     dgain, dbias, dg_stride);
-  hipLaunchKernelGGL(k_bnb_fin2, dim3((unsigned)cdiv(C, 64)), dim3(1024), 0, st, p1, p2, nch, B, C, gain,
-                     tab_stride, (int64_t)B * HW, dgain, dbias, A, Bc, dg_stride);
+  hipLaunchKernelGGL(k_bnb_fin, dim3((unsigned)cdiv(C, 64)), dim3(1024), 0, st, p1, p2, nch, B, C, gain, tab_stride,
+                     (int64_t)B * HW, dgain, dbias, A, Bc, dg_stride);
   ps.done_bytes("bn_bwd_stats", gbytes + xbytes);
   const int64_t M = (int64_t)B * HW;
   const int CC = Cp / 8;
