@@ -124,7 +124,10 @@ void im2col_grad(hipStream_t st, const float* dcol, int N, int H, int W, float* 
 // keeps full precision).  The 27 filter columns n = co * 9 + r * 3 + s (27 of
 // a 32-wide tile) are the N side of both products; the 3x3 window turns into
 // 9-term gathers around them.
-constexpr int kHR = 16;     // output rows per forward block
+// output rows per forward block: 16, or 8 where that leaves less than 512
+// blocks (two per CU hide each other's row steps; the two extra Z rows of a
+// block cost 1/8 more products)
+static int ghead_rows(int B, int H, int ncb) { return (int64_t)B * cdiv(H, 16) * ncb >= 512 ? 16 : 8; }
 constexpr int kZS = 33;     // LDS floats per Z position (odd: conflict-free gathers)
 constexpr int kZP = 130;    // Z positions per ring row: 128 output columns + 2 halo
 
@@ -138,7 +141,7 @@ static int ghead_cols(int W) { return W <= 128 ? W : 126; }
 // Forward.  Z[q][n] = sum_c a[q][c] W[n][c] for every input position q (K =
 // the channels, each input value read once), then img[p][co] = tanh(sum_{r,s}
 // Z[p + (r - 1, s - 1)][co * 9 + r * 3 + s] / sigma + b[co]).  A block takes
-// kHR output rows x ghead_cols(W) output columns of one image and walks its Z
+// TH output rows x ghead_cols(W) output columns of one image and walks its Z
 // rows top to bottom: each of the 4 waves computes one 32-position tile of a
 // Z row into a 3-row LDS ring (rows outside the image are never read), then
 // the block gathers the output row whose three Z rows are present.  A wave
@@ -146,7 +149,7 @@ static int ghead_cols(int W) { return W <= 128 ? W : 126; }
 // A lane of the product holds position l % 32 and channels 16 j + 8 (l / 32)
 // + 0..7 of chunk j: one 16-byte load feeds 8 products.
 template <int CK>   // CK = Cp / 16
-__global__ __launch_bounds__(256, 2) void k_ghead_fwd(const bf16_t* __restrict__ x, int H, int W, int C, int TC,
+__global__ __launch_bounds__(256, 2) void k_ghead_fwd(const bf16_t* __restrict__ x, int H, int W, int C, int TC, int TH,
                                                       const float* __restrict__ mean, const float* __restrict__ scale,
                                                       const float* __restrict__ shift, const float* __restrict__ Wt,
                                                       const float* __restrict__ sigma, const float* __restrict__ bias,
@@ -168,14 +171,14 @@ __global__ __launch_bounds__(256, 2) void k_ghead_fwd(const bf16_t* __restrict__
     reinterpret_cast<float*>(cst[1])[c] = ok ? scale[c] : 0.f;
     reinterpret_cast<float*>(cst[2])[c] = ok ? shift[c] : 0.f;
   }
-  const int ncb = (W + TC - 1) / TC, nrb = (H + kHR - 1) / kHR;
+  const int ncb = (W + TC - 1) / TC, nrb = (H + TH - 1) / TH;
   int bid = blockIdx.x;
   const int cb = bid % ncb;
   bid /= ncb;
   const int rb = bid % nrb;
   const int b = bid / nrb;
-  const int w0 = cb * TC, h0 = rb * kHR;
-  const int w1 = min(W, w0 + TC), h1 = min(H, h0 + kHR);
+  const int w0 = cb * TC, h0 = rb * TH;
+  const int w1 = min(W, w0 + TC), h1 = min(H, h0 + TH);
   const int zc0 = max(0, w0 - 1), zc1 = min(W, w1 + 1);   // Z columns the block needs
   const bool has_tile = 32 * wv < zc1 - zc0;
   const int zw = zc0 + 32 * wv + ln;                        // this lane's Z column
@@ -281,89 +284,199 @@ __global__ __launch_bounds__(256, 2) void k_ghead_fwd(const bf16_t* __restrict__
   }
 }
 
-// da[p][c] = sum_{tap, co} dt[p - tap][co] * W[co][tap][c] / sigma,
-// dt = dimg * (1 - img^2) (dimg has channel stride ldd >= 3).  A block
-// computes a 2-row x 64-column tile of pixels, all Cp channels: dt of the
-// haloed tile is staged in LDS once ([row][col][4], one 16-byte read per
-// position), the weights as [tap*3][Cp] scaled by 1/sigma (zero for
-// channels >= C).  A work item is 4 consecutive channels x 4 consecutive
-// pixels of a row: 432 FMAs per 18 + 27 LDS reads, one 16-byte store per
-// pixel (lanes run over channels, so the stores are contiguous).
-constexpr int kDR = 2;     // output rows per block
-constexpr int kDC = 64;    // output columns per block
+// Backward through the conv, the ReLU and the batch norm without the gradient
+// of their operand in memory: for every position p and channel c
+//   da = sum_n G[p][n] W[n][c] / sigma,  G[p][co * 9 + r * 3 + s] = dt[p - (r - 1, s - 1)][co],
+//   dt = dimg (1 - img^2)   (dimg has channel stride ldd >= 3),
+//   dz = da [gain xhat + bias > 0],  xhat = (x - mean) rstd,
+// formed in fp32 on the matrix cores (27 products per value) in both passes:
+// pass 1 (APPLY false) sums dz and dz * xhat per block of TR rows of an image,
+// pass 2 writes dx = rstd (gain dz - A - xhat Bc) from their totals.  da took
+// 4 bytes per value written once and read twice: at 32 x 128 x 128 x 96 the
+// three kernels 58 + 54 + 64 us, these 30 + 46.
+// The channels are the M side, the positions the N side of the product, with
+// the rows of the filter operand permuted so that a lane ends with 16
+// consecutive channels of one position (16-byte loads and stores of x and
+// dx).  A wave owns 32 channels, so that its filter operand, constants and
+// sums stay in registers (all of 96 channels per wave: 244 spilled, 211 us a
+// pass), and its block's NG wave groups stride the positions.  dt of the
+// block's rows plus a one-pixel zero frame is staged in
+// LDS as in the weight gradient, so G is 14 reads per position pair.
+constexpr size_t kBnbLds = 64 * 1024;
+static size_t ghead_bnb_lds_at(int tr, int W, int Cp) {
+  return ((size_t)(tr + 2) * (W + 2) * 3 + 3) / 4 * 16 + (8 + 6) * (size_t)Cp * 4;
+}
+// rows per block: up to 8, fewer while that leaves less than 512 blocks or does not fit in LDS
+static int ghead_bnb_rows(int B, int H, int W, int Cp) {
+  int tr = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)B * H / 512));
+  while (tr > 1 && ghead_bnb_lds_at(tr, W, Cp) > kBnbLds) --tr;
+  return tr;
+}
 
-__global__ __launch_bounds__(256) void k_ghead_dgrad(const float* __restrict__ dimg, int ldd,
-                                                     const float* __restrict__ img, int B, int H, int W, int C,
-                                                     int Cp, const float* __restrict__ Wt,
-                                                     const float* __restrict__ sigma, float* __restrict__ da) {
-  __shared__ float4 dts[kDR + 2][kDC + 2];
-  extern __shared__ float4 wsd4[];    // [27][Cp / 4]
-  float* wsd = reinterpret_cast<float*>(wsd4);
+constexpr int bnb_groups(int ct) { return ct == 1 ? 4 : 2; }
+template <int CT, bool APPLY>   // CT = Cp / 32
+__global__ __launch_bounds__(64 * CT * bnb_groups(CT), 3) void k_ghead_bnb(
+    const float* __restrict__ dimg, int ldd, const float* __restrict__ img, const bf16_t* __restrict__ x, int H, int W,
+    FastDiv fdW, FastDiv fdW2, int C, int TR, const float* __restrict__ Wt, const float* __restrict__ sigma,
+    const float* __restrict__ mean, const float* __restrict__ rstd, const float* __restrict__ gain,
+    const float* __restrict__ bias, const float* __restrict__ A, const float* __restrict__ Bc, float* __restrict__ p1,
+    float* __restrict__ p2, bf16_t* __restrict__ dx) {
+  constexpr int Cp = 32 * CT, NT = 14;   // 27 filter columns in 14 products of two
+  constexpr int NG = bnb_groups(CT), NTH = 64 * CT * NG;
+  extern __shared__ float4 sm4[];
+  const int W2 = W + 2;
+  float* const dts = reinterpret_cast<float*>(sm4);                   // [(rows + 2) * W2][3]
+  float* const red = dts + ((TR + 2) * W2 * 3 + 3) / 4 * 4;          // [NG][2][Cp]
+  const int nrb = (H + TR - 1) / TR;
+  const int b = blockIdx.x / nrb, h0 = (blockIdx.x % nrb) * TR;
+  const int nr = min(TR, H - h0);
+  const int tid = threadIdx.x, lane = tid & 63, kh = lane >> 5, ln = lane & 31;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ct = wv % CT, grp = wv / CT;
+#pragma unroll 2
+  for (int i = tid; i < (nr + 2) * W2; i += NTH) {
+    const int rr = (int)fdiv((uint32_t)i, fdW2), cc = i - rr * W2;
+    const int h = h0 - 1 + rr, w = cc - 1;
+    float d[3] = {0.f, 0.f, 0.f};
+    if ((unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W) {
+      const int64_t q = ((int64_t)b * H + h) * W + w;
+#pragma unroll
+      for (int co = 0; co < 3; ++co) {
+        const float y = img[q * 3 + co];
+        d[co] = dimg[q * ldd + co] * (1.f - y * y);
+      }
+    }
+#pragma unroll
+    for (int co = 0; co < 3; ++co) dts[3 * i + co] = d[co];
+  }
+  // filter operand: row ln is channel 32 ct + perm; product t takes column 2 t + kh
+  const int cf = 32 * ct + 16 * ((ln >> 2) & 1) + 4 * (ln >> 3) + (ln & 3);
   const float inv = 1.f / *sigma;
-  for (int i = threadIdx.x; i < 27 * Cp; i += 256) {
-    const int k = i / Cp, c = i - k * Cp;
-    wsd[i] = c < C ? Wt[k * C + c] * inv : 0.f;
+  float wr[NT];
+  int off[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int n = 2 * t + kh, co = n / 9, tap = n - 9 * co;
+    off[t] = n < 27 ? ((2 - tap / 3) * W2 + (2 - tap % 3)) * 3 + co : 0;
+    wr[t] = n < 27 && cf < C ? Wt[n * C + cf] * inv : 0.f;
   }
-  const int tiles_w = (W + kDC - 1) / kDC, tiles_h = (H + kDR - 1) / kDR;
-  int bid = blockIdx.x;
-  const int tw = bid % tiles_w;
-  bid /= tiles_w;
-  const int th = bid % tiles_h;
-  const int b = bid / tiles_h;
-  const int h0 = th * kDR, w0 = tw * kDC;
-  for (int idx = threadIdx.x; idx < (kDR + 2) * (kDC + 2); idx += 256) {
-    const int r = idx / (kDC + 2), col = idx - r * (kDC + 2);
-    const int oh = h0 + r - 1, ow = w0 + col - 1;
-    float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
-    if ((unsigned)oh < (unsigned)H && (unsigned)ow < (unsigned)W) {
-      const int64_t q = ((int64_t)b * H + oh) * W + ow;
-      const float y0 = img[q * 3], y1 = img[q * 3 + 1], y2 = img[q * 3 + 2];
-      d.x = dimg[q * ldd] * (1.f - y0 * y0);
-      d.y = dimg[q * ldd + 1] * (1.f - y1 * y1);
-      d.z = dimg[q * ldd + 2] * (1.f - y2 * y2);
-    }
-    dts[r][col] = d;
+  // this lane's 16 channels from c0; the channel constants stay in LDS (read
+  // by 16 bytes, the same address in all lanes of a half): in registers they
+  // leave room for one block per CU only
+  const int c0 = 32 * ct + 16 * kh;
+  float* const cst = red + 2 * NG * Cp;   // [6][Cp]: zero for padded channels
+  for (int c = tid; c < Cp; c += NTH) {
+    const bool ok = c < C;
+    cst[c] = ok ? mean[c] : 0.f;
+    cst[Cp + c] = ok ? rstd[c] : 0.f;
+    cst[2 * Cp + c] = ok ? gain[c] : 0.f;
+    cst[3 * Cp + c] = ok ? bias[c] : 0.f;
+    cst[4 * Cp + c] = APPLY && ok ? A[c] : 0.f;
+    cst[5 * Cp + c] = APPLY && ok ? Bc[c] : 0.f;
   }
+  const int P = nr * W;
+  const int nch = (P + 31) / 32;
+  const int64_t base = (int64_t)(b * H + h0) * W;
+  // two chunks of x in flight
+  constexpr int PD = 2;
+  uint4 xr[PD][2];
+  auto fetch = [&](int k, uint4 (&q)[2]) {
+    const int pos = min(k * 32 + ln, P - 1);
+    const bf16_t* src = x + (base + pos) * Cp + c0;
+    q[0] = *reinterpret_cast<const uint4*>(src);
+    q[1] = *reinterpret_cast<const uint4*>(src + 8);
+  };
+  float s1[APPLY ? 1 : 16], s2[APPLY ? 1 : 16];
+#pragma unroll
+  for (int e = 0; e < (APPLY ? 1 : 16); ++e) s1[e] = s2[e] = 0.f;
+#pragma unroll
+  for (int u = 0; u < PD; ++u)
+    if (grp + u * NG < nch) fetch(grp + u * NG, xr[u]);
   __syncthreads();
-  const int ncg = Cp >> 2;
-  const int items = ncg * kDR * (kDC / 4);
-  for (int it = threadIdx.x; it < items; it += 256) {
-    const int cg = it % ncg, pq = it / ncg;
-    const int rr = pq / (kDC / 4), cq = pq - rr * (kDC / 4);
-    const int oh = h0 + rr, ow0 = w0 + 4 * cq;
-    if (oh >= H || ow0 >= W) continue;
-    float acc[4][4];
+  auto chunk = [&](int k, uint4 (&q)[2]) {
+    const uint4 c0q = q[0], c1q = q[1];
+    const int pos = min(k * 32 + ln, P - 1);   // clamped: its values are not used
+    const bool valid = k * 32 + ln < P;
+    const int64_t o0 = (base + pos) * Cp + c0;
+    const int hrow = (int)fdiv((uint32_t)pos, fdW);
+    const float* g0 = dts + (hrow * W2 + (pos - hrow * W)) * 3;
+    float g[NT];
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
+    for (int t = 0; t < NT; ++t) g[t] = g0[off[t]];
+    if (kh) g[NT - 1] = 0.f;   // column 27 does not exist
+    if (k + PD * NG < nch) fetch(k + PD * NG, q);
+    f32x16 da;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[p][e] = 0.f;
-    // output pixel (oh, ow0 + p) takes dt at (oh - r + 1, ow0 + p - s + 1) =
-    // staged position (rr + 2 - r, 4 cq + p + 2 - s)
+    for (int r = 0; r < 16; ++r) da[r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < 3; ++r) {
-      float4 d[6];
+    for (int t = 0; t < NT; ++t) da = mfma_f32(wr[t], g[t], da);
+    float xv[16];
+    unpack8(c0q, xv);
+    unpack8(c1q, xv + 8);
+    float o[APPLY ? 16 : 1];
+    const float4* c4 = reinterpret_cast<const float4*>(cst + c0);
+    asm volatile("" ::: "memory");   // (keeps the compiler from hoisting the constants out of the loop)
 #pragma unroll
-      for (int j = 0; j < 6; ++j) d[j] = dts[rr + 2 - r][4 * cq + j];
+    for (int q = 0; q < 4; ++q) {
+      const float4 mu4 = c4[q], rs4 = c4[Cp / 4 + q], ga4 = c4[2 * Cp / 4 + q], be4 = c4[3 * Cp / 4 + q];
+      const float mu[4] = {mu4.x, mu4.y, mu4.z, mu4.w}, rs[4] = {rs4.x, rs4.y, rs4.z, rs4.w};
+      const float ga[4] = {ga4.x, ga4.y, ga4.z, ga4.w}, be[4] = {be4.x, be4.y, be4.z, be4.w};
+      float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f), b4 = a4;
+      if constexpr (APPLY) {
+        a4 = c4[4 * Cp / 4 + q];
+        b4 = c4[5 * Cp / 4 + q];
+      }
+      const float aa[4] = {a4.x, a4.y, a4.z, a4.w}, bb[4] = {b4.x, b4.y, b4.z, b4.w};
 #pragma unroll
-      for (int s_ = 0; s_ < 3; ++s_)
-#pragma unroll
-        for (int co = 0; co < 3; ++co) {
-          const float4 wv = wsd4[(co * 9 + r * 3 + s_) * ncg + cg];
-#pragma unroll
-          for (int p = 0; p < 4; ++p) {
-            const float4 dd = d[p + 2 - s_];
-            const float dv = co == 0 ? dd.x : (co == 1 ? dd.y : dd.z);
-            acc[p][0] = fmaf(dv, wv.x, acc[p][0]);
-            acc[p][1] = fmaf(dv, wv.y, acc[p][1]);
-            acc[p][2] = fmaf(dv, wv.z, acc[p][2]);
-            acc[p][3] = fmaf(dv, wv.w, acc[p][3]);
-          }
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * q + e;
+        const float xh = (xv[r] - mu[e]) * rs[e];
+        const float dz = ga[e] * xh + be[e] > 0.f && valid ? da[r] : 0.f;
+        if constexpr (APPLY) {
+          o[r] = rs[e] * (ga[e] * dz - aa[e] - xh * bb[e]);
+        } else {
+          s1[r] += dz;
+          s2[r] = fmaf(dz, xh, s2[r]);
         }
+      }
     }
-    const int64_t q0 = ((int64_t)b * H + oh) * W + ow0;
+    if constexpr (APPLY) {
+      if (valid) {   // (padded channels: rstd is 0 there, so they get 0)
+        *reinterpret_cast<uint4*>(dx + o0) = pack8(o);
+        *reinterpret_cast<uint4*>(dx + o0 + 8) = pack8(o + 8);
+      }
+    }
+  };
+  for (int k = grp; k < nch; k += PD * NG)
 #pragma unroll
-    for (int p = 0; p < 4; ++p)
-      *reinterpret_cast<float4*>(da + (q0 + p) * Cp + 4 * cg) = make_float4(acc[p][0], acc[p][1], acc[p][2], acc[p][3]);
+    for (int u = 0; u < PD; ++u)
+      if (k + u * NG < nch) chunk(k + u * NG, xr[u]);
+  if constexpr (!APPLY) {
+    // sums over the 32 positions of each lane half, then over the groups in order
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      float a = s1[e], c = s2[e];
+#pragma unroll
+      for (int m = 16; m > 0; m >>= 1) {
+        a += __shfl_xor(a, m, 64);
+        c += __shfl_xor(c, m, 64);
+      }
+      if (ln == 0) {
+        red[(2 * grp) * Cp + c0 + e] = a;
+        red[(2 * grp + 1) * Cp + c0 + e] = c;
+      }
+    }
+    __syncthreads();
+    for (int c = tid; c < C; c += NTH) {
+      float a = 0.f, d = 0.f;
+#pragma unroll
+      for (int w = 0; w < NG; ++w) {
+        a += red[2 * w * Cp + c];
+        d += red[(2 * w + 1) * Cp + c];
+      }
+      p1[(int64_t)blockIdx.x * C + c] = a;
+      p2[(int64_t)blockIdx.x * C + c] = d;
+    }
   }
 }
 
@@ -383,17 +496,19 @@ constexpr size_t kWgLds = 64 * 1024;
 static size_t ghead_lds_at(int tr, int W, int Cp) {
   return ((size_t)(tr + 2) * (W + 2) * 3 + 3) / 4 * 16 + (size_t)4 * kWC * (Cp + 4) * 4 + 3 * (size_t)Cp * 4 + 768 * 4;
 }
-// rows per weight-gradient block: about 2048 positions, fewer if the LDS tile would not fit
-static int ghead_wrows(int W, int Cp) {
+// rows per weight-gradient block: about 2048 positions, fewer while that leaves
+// less than 512 blocks (two per CU; 256 blocks: 79 us, 512: 58) or the LDS
+// tile does not fit
+static int ghead_wrows(int B, int H, int W, int Cp) {
   int tr = std::max(1, std::min(16, 2048 / W));
+  tr = (int)std::max<int64_t>(1, std::min<int64_t>(tr, (int64_t)B * H / 512));
   while (tr > 1 && ghead_lds_at(tr, W, Cp) > kWgLds) --tr;
   return tr;
 }
-static size_t ghead_wgrad_lds(int W, int Cp) { return ghead_lds_at(ghead_wrows(W, Cp), W, Cp); }
 
 bool ghead_shape_ok(int W, int C) {
   const int Cp = (int)cpad(C);
-  return C >= 1 && Cp <= 128 && W >= 4 && W % 4 == 0 && ghead_wgrad_lds(W, Cp) <= kWgLds;
+  return C >= 1 && Cp <= 128 && W >= 4 && W % 4 == 0 && ghead_lds_at(1, W, Cp) <= kWgLds;
 }
 
 template <int CT>   // CT = Cp / 32
@@ -563,7 +678,7 @@ __global__ __launch_bounds__(1024) void k_ghead_fin(const float* part, int nch, 
   }
 }
 
-static int64_t ghead_wgrad_blocks(int B, int H, int W, int Cp) { return (int64_t)B * cdiv(H, ghead_wrows(W, Cp)); }
+static int64_t ghead_wgrad_blocks(int B, int H, int W, int Cp) { return (int64_t)B * cdiv(H, ghead_wrows(B, H, W, Cp)); }
 
 size_t ghead_ws_bytes(int B, int H, int W, int C) {
   return align256((size_t)ghead_wgrad_blocks(B, H, W, (int)cpad(C)) * (27 * C + 3) * 4);
@@ -573,11 +688,12 @@ void ghead_fwd(hipStream_t st, const void* x, int B, int H, int W, int C, int Cp
                const float* scale, const float* shift, const float* Wt, const float* sigma, const float* bias,
                float* img) {
   const int TC = ghead_cols(W);
-  const int64_t blocks = (int64_t)B * cdiv(H, kHR) * cdiv(W, TC);
+  const int TH = ghead_rows(B, H, (int)cdiv(W, TC));
+  const int64_t blocks = (int64_t)B * cdiv(H, TH) * cdiv(W, TC);
   PG_CHECK(blocks < (1LL << 31) && Cp == cpad(C) && ghead_shape_ok(W, C), "ghead_fwd: shape");
   const bf16_t* xb = (const bf16_t*)x;
 #define PG_GHF(CK)                                                                                              \
-  hipLaunchKernelGGL(k_ghead_fwd<CK>, dim3((unsigned)blocks), dim3(256), 0, st, xb, H, W, C, TC, mean, scale, \
+  hipLaunchKernelGGL(k_ghead_fwd<CK>, dim3((unsigned)blocks), dim3(256), 0, st, xb, H, W, C, TC, TH, mean, scale, \
                      shift, Wt, sigma, bias, img)
   switch (Cp / 32) {
     case 1: PG_GHF(2); break;
@@ -589,17 +705,14 @@ void ghead_fwd(hipStream_t st, const void* x, int B, int H, int W, int C, int Cp
   PG_LAUNCH_CHECK();
 }
 
-void ghead_bwd(hipStream_t st, const float* dimg, int ldd, const float* img, const void* x, int B, int H, int W,
-               int C, int Cp, const float* mean, const float* scale, const float* shift, const float* Wt,
-               const float* sigma, float* da, float* dwsn, float* dbias, void* ws) {
-  const int64_t dblocks = (int64_t)B * cdiv(H, kDR) * cdiv(W, kDC);
-  PG_CHECK(dblocks < (1LL << 31) && Cp == cpad(C) && ghead_shape_ok(W, C) && ldd >= 3, "ghead_bwd: shape");
-  const int TRW = ghead_wrows(W, Cp);
-  const size_t lds = ghead_wgrad_lds(W, Cp);
+void ghead_wgrad(hipStream_t st, const float* dimg, int ldd, const float* img, const void* x, int B, int H, int W,
+                 int C, int Cp, const float* mean, const float* scale, const float* shift, float* dwsn, float* dbias,
+                 void* ws) {
+  PG_CHECK(Cp == cpad(C) && ghead_shape_ok(W, C) && ldd >= 3, "ghead_wgrad: shape");
+  const int TRW = ghead_wrows(B, H, W, Cp);
+  const size_t lds = ghead_lds_at(TRW, W, Cp);
   const int nch = (int)ghead_wgrad_blocks(B, H, W, Cp);
   const FastDiv fdW = make_fastdiv((uint32_t)W);
-  hipLaunchKernelGGL(k_ghead_dgrad, dim3((unsigned)dblocks), dim3(256), 27 * Cp * sizeof(float), st, dimg, ldd,
-                     img, B, H, W, C, Cp, Wt, sigma, da);
   const bf16_t* xb = (const bf16_t*)x;
 #define PG_GHW(CT)                                                                                                   \
   hipLaunchKernelGGL(k_ghead_wgrad<CT>, dim3(nch), dim3(256), lds, st, dimg, ldd, img, xb, H, W, fdW, C, TRW, mean,  \
@@ -613,6 +726,45 @@ void ghead_bwd(hipStream_t st, const float* dimg, int ldd, const float* img, con
 #undef PG_GHW
   hipLaunchKernelGGL(k_ghead_fin, dim3((unsigned)cdiv(27 * C + 3, 64)), dim3(1024), 0, st, (const float*)ws, nch,
                      27 * C + 3, dwsn, dbias);
+  PG_LAUNCH_CHECK();
+}
+
+size_t ghead_bnb_ws_bytes(int B, int H, int W, int C) {
+  const int Cp = (int)cpad(C);
+  const int64_t nb = (int64_t)B * cdiv(H, ghead_bnb_rows(B, H, W, Cp));
+  return 2 * align256((size_t)nb * C * 4) + 2 * align256((size_t)Cp * 4);
+}
+
+void ghead_bnb(hipStream_t st, const float* dimg, int ldd, const float* img, const void* x, int B, int H, int W, int C,
+               int Cp, const float* Wt, const float* sigma, const float* mean, const float* rstd, const float* gain,
+               const float* bias, void* dx, float* dgain, float* dbias, void* ws) {
+  PG_CHECK(Cp == cpad(C) && ghead_shape_ok(W, C) && ldd >= 3, "ghead_bnb: shape");
+  const int TR = ghead_bnb_rows(B, H, W, Cp), nch = (int)cdiv(H, TR);
+  const int64_t nb = (int64_t)B * nch;
+  PG_CHECK(nb < (1LL << 31) && (int64_t)B * H * W < (1LL << 31), "ghead_bnb: too many pixels");
+  float* p1 = (float*)ws;
+  float* p2 = (float*)((char*)p1 + align256((size_t)nb * C * 4));
+  float* A = (float*)((char*)p2 + align256((size_t)nb * C * 4));
+  float* Bc = (float*)((char*)A + align256((size_t)Cp * 4));
+  const size_t lds = ghead_bnb_lds_at(TR, W, Cp);
+  const FastDiv fdW = make_fastdiv((uint32_t)W), fdW2 = make_fastdiv((uint32_t)W + 2);
+  const bf16_t* xb = (const bf16_t*)x;
+#define PG_GHB(CT, AP)                                                                                            \
+  hipLaunchKernelGGL((k_ghead_bnb<CT, AP>), dim3((unsigned)nb), dim3(64 * CT * bnb_groups(CT)), lds, st, dimg,    \
+                     ldd, img, xb, H, W, fdW, fdW2, C, TR, Wt, sigma, mean, rstd, gain, bias, A, Bc, p1, p2,      \
+                     (bf16_t*)dx)
+#define PG_GHB4(AP)                \
+  switch (Cp / 32) {               \
+    case 1: PG_GHB(1, AP); break;  \
+    case 2: PG_GHB(2, AP); break;  \
+    case 3: PG_GHB(3, AP); break;  \
+    default: PG_GHB(4, AP); break; \
+  }
+  PG_GHB4(false)
+  bn_bwd_finish(st, p1, p2, nch, B, C, gain, 0, (int64_t)B * H * W, dgain, dbias, A, Bc, 0);
+  PG_GHB4(true)
+#undef PG_GHB4
+#undef PG_GHB
   PG_LAUNCH_CHECK();
 }
 

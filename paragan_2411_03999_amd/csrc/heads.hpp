@@ -20,9 +20,14 @@ void ghead_fwd(hipStream_t st, const void* x, int B, int H, int W, int C, int Cp
                const float* scale, const float* shift, const float* Wt, const float* sigma, const float* bias,
                float* img);
 // da: fp32 [B][H][W][Cp] gradient of relu(bn(x)); dwsn: [3][3][3][C] gradient of W/sigma
-void ghead_bwd(hipStream_t st, const float* dimg, int ldd, const float* img, const void* x, int B, int H, int W,
-               int C, int Cp, const float* mean, const float* scale, const float* shift, const float* Wt,
-               const float* sigma, float* da, float* dwsn, float* dbias, void* ws);
+void ghead_wgrad(hipStream_t st, const float* dimg, int ldd, const float* img, const void* x, int B, int H, int W,
+                 int C, int Cp, const float* mean, const float* scale, const float* shift, float* dwsn, float* dbias,
+                 void* ws);
+// the gradient through conv, ReLU and batch norm to x (per-channel gain and bias)
+size_t ghead_bnb_ws_bytes(int B, int H, int W, int C);
+void ghead_bnb(hipStream_t st, const float* dimg, int ldd, const float* img, const void* x, int B, int H, int W, int C,
+               int Cp, const float* Wt, const float* sigma, const float* mean, const float* rstd, const float* gain,
+               const float* bias, void* dx, float* dgain, float* dbias, void* ws);
 
 // projection-discriminator head (fp32) and hinge loss
 void dhead_fwd(hipStream_t st, const void* x, int N, int HW, int C, int Cp, const int32_t* y, const float* w,

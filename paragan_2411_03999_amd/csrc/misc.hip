@@ -1454,6 +1454,12 @@ __global__ __launch_bounds__(256) void k_bnb_apply(const float* g, int g_up2, co
   }
 }
 
+void bn_bwd_finish(hipStream_t st, const float* p1, const float* p2, int nch, int B, int C, const float* gain,
+                   int tab_stride, int64_t N, float* dgain, float* dbias, float* A, float* Bc, int dg_stride) {
+  hipLaunchKernelGGL(k_bnb_fin, dim3((unsigned)cdiv(C, 64)), dim3(1024), 0, st, p1, p2, nch, B, C, gain, tab_stride, N,
+                     dgain, dbias, A, Bc, dg_stride);
+}
+
 size_t bn_bwd_ws_bytes(int B, int HW, int C) {
   const BnbShape sh = bnb_shape(B, HW, C);
   return 2 * align256((size_t)B * sh.nchs * C * 4) + 2 * align256((size_t)cpad(C) * 4);
@@ -1485,8 +1491,7 @@ void bn_bwd(hipStream_t st, bool f32, const float* g, bool g_up2, const void* x,
   else
     hipLaunchKernelGGL(k_bnb_reduce<bf16_t>, g1, dim3(256), 0, st, g, (int)g_up2, (const bf16_t*)x, HW, H, W, fdW,
                        C, Cp, mean, rstd, gain, bias, tab_stride, sh, p1, p2);
-  hipLaunchKernelGGL(k_bnb_fin, dim3((unsigned)cdiv(C, 64)), dim3(1024), 0, st, p1, p2, nch, B, C, gain, tab_stride,
-                     (int64_t)B * HW, dgain, dbias, A, Bc, dg_stride);
+  bn_bwd_finish(st, p1, p2, nch, B, C, gain, tab_stride, (int64_t)B * HW, dgain, dbias, A, Bc, dg_stride);
   ps.done_bytes("bn_bwd_stats", gbytes + xbytes);
   const int64_t M = (int64_t)B * HW;
   const int CC = Cp / 8;

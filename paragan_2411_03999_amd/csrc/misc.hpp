@@ -97,6 +97,10 @@ void cbn_tables(hipStream_t st, const float* cond, int dc, const float* Wg, cons
                 const float* sg, const float* sb, const float* gain_p, const float* bias_p,
                 const float* rstd, int B, int C, int Cp, float* gain, float* bias, float* scale);
 size_t bn_bwd_ws_bytes(int B, int HW, int C);
+// the step between the sums p1, p2 ([B][nch][C]: dz, dz * xhat) and dx: the
+// totals A, Bc and the gain / bias gradients
+void bn_bwd_finish(hipStream_t st, const float* p1, const float* p2, int nch, int B, int C, const float* gain,
+                   int tab_stride, int64_t N, float* dgain, float* dbias, float* A, float* Bc, int dg_stride);
 void bn_bwd(hipStream_t st, bool f32, const float* g, bool g_up2, const void* x, int B, int H, int W,
             int C, int Cp, const float* mean, const float* rstd, const float* gain, const float* bias,
             int tab_stride, const float* res, void* dx, float* dgain, float* dbias, int dg_stride,

@@ -297,7 +297,7 @@ void GOut::plan_saved(Arena& s) {
 }
 
 struct GOutWs {
-  float *da, *dw, *part;
+  float *dw, *part;
   void* red;           // reductions, the SN iteration and the weight-gradient partials, in turn
   size_t red_bytes;
 };
@@ -305,10 +305,9 @@ struct GOutWs {
 static GOutWs gout_carve(const GOut& g, Arena& w) {
   const int64_t M = (int64_t)g.B * g.H * g.W;
   GOutWs r;
-  r.da = w.f32((size_t)M * cpad(g.C));
   r.dw = w.f32(27LL * g.C);
   r.part = w.f32(kSnbParts);
-  r.red_bytes = std::max({ghead_ws_bytes(g.B, g.H, g.W, g.C), bn_bwd_ws_bytes(g.B, g.H * g.W, g.C),
+  r.red_bytes = std::max({ghead_ws_bytes(g.B, g.H, g.W, g.C), ghead_bnb_ws_bytes(g.B, g.H, g.W, g.C),
                           bn_stats_ws_bytes(M, g.C), sn_ws_bytes(3, 27LL * g.C)});
   r.red = w.bytes(r.red_bytes);
   return r;
@@ -338,11 +337,10 @@ void GOut::bwd(const Exec& ex, const Params& P, const void* x, const float* img,
   const GOutWs r = gout_carve(*this, w);
   PG_CHECK(w.off <= ex.ws_bytes, "output layer: workspace too small");
   const int cp = (int)cpad(C);
-  ghead_bwd(ex.st, dimg, ldd, img, x, B, H, W, C, cp, mean_, scale_, bias_, P.w("out_conv.w"), sn_.sigma, r.da,
-            r.dw, P.gr("out_conv.b"), r.red);
+  ghead_wgrad(ex.st, dimg, ldd, img, x, B, H, W, C, cp, mean_, scale_, bias_, r.dw, P.gr("out_conv.b"), r.red);
   sn_bwd(ex.st, r.dw, P.w("out_conv.w"), sn_.u, sn_.v, sn_.sigma, 3, C, 3, C, nullptr, P.gr("out_conv.w"), r.part);
-  bn_bwd(ex.st, false, r.da, false, x, B, H, W, C, cp, mean_, rstd_, gain_, bias_, 0, nullptr, dx,
-         P.gr("out_bn.gain"), P.gr("out_bn.bias"), 0, r.red);
+  ghead_bnb(ex.st, dimg, ldd, img, x, B, H, W, C, cp, P.w("out_conv.w"), sn_.sigma, mean_, rstd_, gain_, bias_, dx,
+            P.gr("out_bn.gain"), P.gr("out_bn.bias"), r.red);
 }
 
 // =================================================================== D
