@@ -606,6 +606,9 @@ struct StepRun {
 void g_sample(paragan_ctx* ctx, const paragan_biggan_desc* d, paragan_net_state* G, const float* z,
               const int32_t* y, float* img, void* ws) {
   StepRun R(ctx, d, G, nullptr, ws);
+  // every SN weight and pack of the network in one group of launches, as the
+  // fused step does (module by module: five launches for each of eight modules)
+  R.g.prep(R.st, R.PG, R.r.side);
   R.g.fwd(R.ex, R.PG, z, y, img, false);
 }
 
@@ -614,6 +617,7 @@ void d_step(paragan_ctx* ctx, const paragan_biggan_desc* d, paragan_net_state* D
   StepRun R(ctx, d, nullptr, D, ws);
   R.stage_real(x_real, y_real, y_fake);
   PG_HIP(hipMemcpyAsync(R.fake_half(), x_fake, (size_t)R.B * R.pix * 3 * 4, hipMemcpyDeviceToDevice, R.st));
+  R.d2.prep(R.st, R.PD, R.r.side, true);
   R.d_update(d, D, R.r.dloss);
   R.losses_to_host(loss_host, 1);
 }
@@ -621,7 +625,8 @@ void d_step(paragan_ctx* ctx, const paragan_biggan_desc* d, paragan_net_state* D
 void g_step(paragan_ctx* ctx, const paragan_biggan_desc* d, paragan_net_state* G, paragan_net_state* D,
             const float* z, const int32_t* y, void* ws, float* loss_host) {
   StepRun R(ctx, d, G, D, ws);
-  R.g_update(d, G, z, y, R.r.dloss, [] {});
+  R.g.prep(R.st, R.PG, R.r.side, true);
+  R.g_update(d, G, z, y, R.r.dloss, [&] { R.d1.prep(R.st, R.PD, R.r.side, true); });
   R.losses_to_host(loss_host, 1);
 }
 
