@@ -398,92 +398,107 @@ __global__ __launch_bounds__(256) void k_conv_f32mfma(ConvK k) {
   }
 }
 
-// The same product for grids that leave CUs idle (the fp32 configuration's
-// own sizes: 1024 pixels x 64 channels is 16 tiles of 64 x 64, each 36 K
-// steps of load, barrier, eight products, barrier: 39 us).  A block takes a
-// 32 x 32 tile and its four waves a quarter of the K steps each, with the
-// operands straight from memory in registers: a lane's four consecutive
-// channels of its row feed four products (lanes below 32 the channels 8 q ..
-// 8 q + 3, the others 8 q + 4 .. 8 q + 7, of both operands alike), and the
-// next 32 channels' loads are in flight during this step's 16 products.  The
-// waves' sums combine in wave order through LDS.  1024 pixels x 64 x 576:
-// 39 -> 11 us.
+// The same product, bit for bit, for grids that leave CUs idle (the fp32
+// configuration's own sizes: 1024 pixels x 64 channels is 16 tiles of 64 x
+// 64, each 36 K steps of load, barrier, eight products, barrier: 1024 x 64 x
+// 576 takes 36 us there, 14 here).  A ReLU decision near zero turns with the
+// last bit of a sum, so the sums keep the tiled kernel's order: the fp32
+// matrix instructions add their products one by one, lowest K index first,
+// whatever their shape, and a wave here runs an output's whole K chain, tap
+// by tap and channel by channel, through v_mfma_f32_16x16x4_f32 (four waves
+// with a quarter of K each took 12 us, and turned decisions).  A block is 32
+// pixels x 32 channels, one 16 x 16 quarter a wave, with the operands
+// straight from memory in registers, NB steps of 32 channels in flight: a
+// lane loads four consecutive channels of its row (lane / 16 names which four
+// of 16), and a 4 x 4 transpose over the lane groups gives it the channels
+// 4 t + lane / 16 that product t takes.
 template <int GATHER, bool RELU>
 __global__ __launch_bounds__(256) void k_conv_f32r(ConvK k) {
-  __shared__ float red[4][16][64];
+  constexpr int NB = 6;
   const AOp& a = k.a;
   const int tmi = blockIdx.x / k.tiles_n, tni = blockIdx.x - tmi * k.tiles_n;
-  const int64_t m = (int64_t)tmi * 32 + (threadIdx.x & 31);
-  const int n0 = tni * 32;
-  const int lane = threadIdx.x & 63, l32 = lane & 31, kh = lane >> 5;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, kq = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const bool mv = m < a.M, nv = n0 + l32 < k.Np;
+  const int64_t m = (int64_t)tmi * 32 + 16 * (wave >> 1) + l16;
+  const int n0 = tni * 32 + 16 * (wave & 1);
+  const bool mv = m < a.M, nv = n0 + l16 < k.Np;
   int b, oh, ow;
   decode_m(mv ? m : 0, a.H, a.W, k.o.pool, b, oh, ow);
   const float* X = (const float*)a.x;
-  const int RR = a.R * a.R, cch = a.C / 32;
-  const float* wrow = (const float*)k.w + (int64_t)(nv ? n0 + l32 : 0) * RR * a.C + 4 * kh;
-  const int per = (RR * cch + 3) >> 2;
-  const int s0 = wave * per, s1 = min(s0 + per, RR * cch);
-  float4 wv[2][4], xv[2][4];
-  auto load = [&](int st, float4 (&w4)[4], float4 (&x4)[4]) {
-    const int tap = st / cch, c0 = (st - tap * cch) * 32 + 4 * kh;
+  const int RR = a.R * a.R, cch = a.C / 32, S = RR * cch;
+  const float* wrow = (const float*)k.w + (int64_t)(nv ? n0 + l16 : 0) * RR * a.C;
+  float wv[NB][2][4], xv[NB][2][4];
+  auto load = [&](int st, float (&w8)[2][4], float (&x8)[2][4]) {
+    const int tap = st / cch, c0 = (st - tap * cch) * 32 + 4 * kq;
     const int r = tap / a.R, s = tap - r * a.R;
     const int ih = oh + r - a.pad, iw = ow + s - a.pad;
     const bool ok = mv && ih >= 0 && ih < a.H && iw >= 0 && iw < a.W;
     int64_t off[4] = {0, 0, 0, 0};
     const int ns = src_offsets<GATHER>(a, b, ok ? ih : 0, ok ? iw : 0, c0, off);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      w4[q] = nv ? *reinterpret_cast<const float4*>(wrow + (int64_t)tap * a.C + c0 - 4 * kh + 8 * q)
-                 : make_float4(0.f, 0.f, 0.f, 0.f);
-      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int q = 0; q < 2; ++q) {
+      float4 w = make_float4(0.f, 0.f, 0.f, 0.f), x = w;
+      if (nv) w = *reinterpret_cast<const float4*>(wrow + (int64_t)tap * a.C + c0 + 16 * q);
       if (ok) {
 #pragma unroll
         for (int d = 0; d < 4; ++d)
           if (d < ns) {
-            const float4 t = *reinterpret_cast<const float4*>(X + off[d] + 8 * q);
-            if (d == 0) v = t;
-            else { v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w; }
+            const float4 t = *reinterpret_cast<const float4*>(X + off[d] + 16 * q);
+            if (d == 0) x = t;
+            else { x.x += t.x; x.y += t.y; x.z += t.z; x.w += t.w; }
           }
       }
-      x4[q] = v;
+      w8[q][0] = w.x; w8[q][1] = w.y; w8[q][2] = w.z; w8[q][3] = w.w;
+      x8[q][0] = x.x; x8[q][1] = x.y; x8[q][2] = x.z; x8[q][3] = x.w;
     }
   };
-  auto xf = [&](float v) {
-    v *= a.gscale;
-    return RELU ? fmaxf(v, 0.f) : v;
+  // v[i] of lane group g -> v[g] of lane group i
+  auto transpose = [](float (&v)[4]) {
+    auto swap32 = [](float& p, float& q) {   // upper half of p with lower half of q
+      const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+      p = __uint_as_float(r[0]);
+      q = __uint_as_float(r[1]);
+    };
+    auto swap16 = [](float& p, float& q) {   // odd groups of p with even groups of q
+      const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(p), __float_as_uint(q), false, false);
+      p = __uint_as_float(r[0]);
+      q = __uint_as_float(r[1]);
+    };
+    swap32(v[0], v[2]);
+    swap32(v[1], v[3]);
+    swap16(v[0], v[1]);
+    swap16(v[2], v[3]);
   };
-  f32x16 acc;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  auto step = [&](float (&w8)[2][4], float (&x8)[2][4]) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  auto step = [&](const float4 (&w4)[4], const float4 (&x4)[4]) {
+    for (int q = 0; q < 2; ++q) {
+      transpose(w8[q]);
+      transpose(x8[q]);
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[q].x, xf(x4[q].x), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[q].y, xf(x4[q].y), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[q].z, xf(x4[q].z), acc, 0, 0, 0);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(w4[q].w, xf(x4[q].w), acc, 0, 0, 0);
+      for (int t = 0; t < 4; ++t) {
+        float x = x8[q][t] * a.gscale;
+        if (RELU) x = fmaxf(x, 0.f);
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w8[q][t], x, acc, 0, 0, 0);
+      }
     }
   };
-  if (s0 < s1) load(s0, wv[0], xv[0]);
-  for (int st = s0; st < s1; st += 2) {
-    if (st + 1 < s1) load(st + 1, wv[1], xv[1]);
-    step(wv[0], xv[0]);
-    if (st + 1 >= s1) break;
-    if (st + 2 < s1) load(st + 2, wv[0], xv[0]);
-    step(wv[1], xv[1]);
-  }
 #pragma unroll
-  for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r];
-  __syncthreads();
+  for (int u = 0; u < NB; ++u)
+    if (u < S) load(u, wv[u], xv[u]);
+  for (int st = 0; st < S; st += NB)
+#pragma unroll
+    for (int u = 0; u < NB; ++u) {
+      if (st + u >= S) break;
+      step(wv[u], xv[u]);
+      if (st + u + NB < S) load(st + u + NB, wv[u], xv[u]);
+    }
   const float accs = (k.o.acc_scale ? *k.o.acc_scale : 1.f) * k.o.acc_mul / (k.o.acc_div ? *k.o.acc_div : 1.f);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int r = 4 * wave + i;
-    float v = (red[0][r][lane] + red[1][r][lane]) + (red[2][r][lane] + red[3][r][lane]);
-    const int col = n0 + i + 8 * wave + 4 * kh;
+    const int col = n0 + 4 * kq + i;
     const float bias = (k.o.bias && col < k.o.n_real) ? k.o.bias[col] : 0.f;
+    float v = acc[i];
     if (!k.o.pool) {
       if (col < k.o.yC && mv) epi_store(k, m, col, v * accs + bias, a.H, a.W);
     } else {   // (as in k_conv_f32mfma)
@@ -548,10 +563,11 @@ void conv_fwd(hipStream_t s, bool f32, const ConvIn& in, int H, int W, int R,
     k.ksteps = R * R * k.cchunks;
     k.tiles_m = (int)cdiv(k.a.M, 64);
     k.tiles_n = (int)cdiv(Np, 64);
-    // 32 x 32 tiles with K over the waves up to 2048 tiles of 64 x 64 (fwd+bwd
-    // of a 96-channel block, 1024 tiles: 920 -> 852 us; of a 128-channel one,
-    // 4096 tiles, whose operands are better shared through LDS: 3576 -> 3905)
-    if (!aff && (int64_t)k.tiles_m * k.tiles_n < 2048) {
+    // one wave a 16 x 16 tile below 384 tiles of 64 x 64 (96 x 864 convs of a
+    // block: at 256 tiles 49 -> 36 us, at 384 tiles 54 either way, at 512
+    // 57 -> 64: with the CUs filled the operands are better shared through
+    // LDS); the sums are the same bits
+    if (!aff && (int64_t)k.tiles_m * k.tiles_n < 384) {
       const std::string name = kname("k_conv_f32r", {in.gather, (int)in.relu});
       k.tiles_m = (int)cdiv(k.a.M, 32);
       k.tiles_n = (int)cdiv(Np, 32);

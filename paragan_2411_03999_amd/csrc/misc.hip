@@ -824,12 +824,14 @@ void sn_bwd(hipStream_t st, const float* dwp, const float* W, const float* u, co
 // ro, ro + P, ... of the chunk, P threads sharing each channel group.  The
 // P partials per channel then combine in order through LDS.  Level 2 merges
 // the chunks.  Chunks are sized so that there are at most kMaxChunks of
-// them: enough blocks to fill the chip, few partials for level 2.  Statistics use shifted sums per thread (shift = the thread's
-// first value, so the sums stay well conditioned) and Chan's parallel
-// variance formula for every merge.
-// rows per thread: 32, down to 8 where that leaves fewer than about 512 blocks
-// (1024 rows of 64 channels: one block of 32 rows per thread, 13 us; four of
-// 8, 5 us), more where 32 would make over kMaxChunks chunks
+// them: enough blocks to fill the chip, few partials for level 2.  Statistics
+// use shifted sums per thread (shift = the thread's first value, so the sums
+// stay well conditioned) and Chan's parallel variance formula for every merge.
+// rows per thread: 32, more where 32 would make over kMaxChunks chunks; sums
+// that no ReLU decision depends on (column sums of a block's own call, the BN
+// backward) go down to 8 where that leaves fewer than about 512 blocks (1024
+// rows of 64 channels: one block of 32 rows per thread, 13 us; four of 8,
+// 5 us)
 constexpr int kRowsPerThread = 32, kRowsMin = 8;
 inline int rows_per_thread(int64_t per_row) {   // per_row: row lanes in all, rows / P
   return (int)std::max<int64_t>(kRowsMin, std::min<int64_t>(kRowsPerThread, cdiv(per_row, 512)));
@@ -839,12 +841,14 @@ constexpr int kMaxChunks = 1024;
 struct RedShape {
   int CC, P, rows_blk;
 };
-// C: channels reduced (real count); the reduction covers cpad(C) channels of M rows
-inline RedShape red_shape(int C, int64_t M) {
+// C: channels reduced (real count); the reduction covers cpad(C) channels of
+// M rows.  fixed: 32 rows per thread whatever the size
+inline RedShape red_shape(int C, int64_t M, bool fixed) {
   RedShape r;
   r.CC = (int)(cpad(C) / 8);
   r.P = std::max(1, 256 / r.CC);
-  const int64_t rpt = std::max<int64_t>(rows_per_thread(cdiv(M, r.P)), cdiv(M, (int64_t)kMaxChunks * r.P));
+  const int64_t rpt = std::max<int64_t>(fixed ? kRowsPerThread : rows_per_thread(cdiv(M, r.P)),
+                                        cdiv(M, (int64_t)kMaxChunks * r.P));
   r.rows_blk = (int)(r.P * rpt);
   return r;
 }
@@ -962,7 +966,7 @@ __global__ __launch_bounds__(1024) void k_colsum_fin(const float* part, int nch,
 }
 
 size_t colsum_ws_bytes(int64_t M, int C) {
-  return align256((size_t)cdiv(M, red_shape(C, M).rows_blk) * C * 4);
+  return align256((size_t)cdiv(M, red_shape(C, M, false).rows_blk) * C * 4);
 }
 
 void colsum(hipStream_t st, bool f32, const void* x, int64_t M, int C, int ldc, float scale, float* out,
@@ -972,7 +976,7 @@ void colsum(hipStream_t st, bool f32, const void* x, int64_t M, int C, int ldc, 
     if (out2) fill(st, out2, C, 0.f);
     return;
   }
-  const RedShape sh = red_shape(C, M);
+  const RedShape sh = red_shape(C, M, false);
   PG_CHECK(ldc >= cpad(C) && ldc % 8 == 0, "colsum: channel stride");
   const int nch = (int)cdiv(M, sh.rows_blk);
   float* part = (float*)ws;
@@ -1032,13 +1036,13 @@ __global__ __launch_bounds__(1024) void k_bn_fin(const float* pmean, const float
 }
 
 size_t bn_stats_ws_bytes(int64_t M, int C) {
-  return 2 * align256((size_t)cdiv(M, red_shape(C, M).rows_blk) * C * 4);
+  return 2 * align256((size_t)cdiv(M, red_shape(C, M, true).rows_blk) * C * 4);
 }
 
 void bn_stats(hipStream_t st, bool f32, const void* x, int64_t M, int C, int ldc, float eps, float* mean,
               float* rstd, void* ws) {
   PG_CHECK(M > 0, "bn_stats: empty batch");
-  const RedShape sh = red_shape(C, M);
+  const RedShape sh = red_shape(C, M, true);
   PG_CHECK(ldc >= cpad(C) && ldc % 8 == 0, "bn_stats: channel stride");
   const int nch = (int)cdiv(M, sh.rows_blk);
   float* pmean = (float*)ws;
