@@ -57,7 +57,7 @@ static AWsB a_carve_b(const Attn& t, Arena& a, int n_cu) {
   w.dwq = a.f32((size_t)t.Nqkv * t.Cp);
   w.dwo = a.f32((size_t)t.Cp * t.dv);
   w.part = a.f32((size_t)kSnbParts * kSnGroupMax);
-  w.wg_bytes = std::max(conv_wgrad_ws(false, M, 1, t.dv, t.Cp, n_cu), conv_wgrad_ws(false, M, 1, t.Cp, t.Nqkv, n_cu));
+  w.wg_bytes = std::max(conv_wgrad_ws(false, M, 1, t.dv, t.Cp, n_cu, t.one_order), conv_wgrad_ws(false, M, 1, t.Cp, t.Nqkv, n_cu, t.one_order));
   w.wg = a.bytes(w.wg_bytes);
   return w;
 }
@@ -122,7 +122,7 @@ void Attn::bwd(const Exec& ex, const Params& P, const void* x, const void* dy, v
   ConvIn ao;
   ao.x = o; ao.B = B; ao.Hx = H; ao.Wx = W; ao.C = dv;
   if (wgrad) {
-    conv_wgrad(ex.st, false, gdy, ao, H, W, 1, Cp, w.dwo, w.wg, w.wg_bytes, ex.n_cu);
+    conv_wgrad(ex.st, false, gdy, ao, H, W, 1, Cp, w.dwo, w.wg, w.wg_bytes, ex.n_cu, one_order);
     attn_dgamma(ex.st, wo, w.dwo, (int64_t)Cp * dv, P.gr("gamma"));
   }
   // dO = gamma * dy Wo
@@ -138,7 +138,7 @@ void Attn::bwd(const Exec& ex, const Params& P, const void* x, const void* dy, v
   gq.g = w.dqkv; gq.Hs = H; gq.Ws = W; gq.C = Nqkv;
   ConvIn ax;
   ax.x = x; ax.B = B; ax.Hx = H; ax.Wx = W; ax.C = Cp;
-  if (wgrad) conv_wgrad(ex.st, false, gq, ax, H, W, 1, Nqkv, w.dwq, w.wg, w.wg_bytes, ex.n_cu);
+  if (wgrad) conv_wgrad(ex.st, false, gq, ax, H, W, 1, Nqkv, w.dwq, w.wg, w.wg_bytes, ex.n_cu, one_order);
   pack_weight_t(ex.st, false, P.w("theta"), sn[0].sigma, C / 8, C, Cp, dk, Nqkv, 0, w.wdq);
   pack_weight_t(ex.st, false, P.w("phi"), sn[1].sigma, C / 8, C, Cp, dk, Nqkv, dk, w.wdq);
   pack_weight_t(ex.st, false, P.w("g"), sn[2].sigma, C / 2, C, Cp, dv, Nqkv, 2 * dk, w.wdq);

@@ -156,10 +156,10 @@ static GWsF g_carve_f(const GBlock& g, Arena& a) {
   w.sn = a.bytes(g_sn_ws(g));
   w.bn = a.bytes(std::max(bn_stats_ws_bytes(M1, g.cin), bn_stats_ws_bytes(M2, g.cout)));
   w.skip = a.f32((size_t)M1 * g.Cop);
-  w.cp_bytes = g.f32 ? 0 : std::max({conv_split_ws(G_SUB, g.B, g.H, g.W, 2, g.Cip, g.Cop),
+  w.cp_bytes = g.f32 || g.one_order ? 0 : std::max({conv_split_ws(G_SUB, g.B, g.H, g.W, 2, g.Cip, g.Cop),
                                      conv_split_ws(G_DIRECT, g.B, g.H, g.W, 1, g.Cip, g.Cop),
                                      conv_split_ws(G_DIRECT, g.B, 2 * g.H, 2 * g.W, 3, g.Cop, g.Cop)});
-  w.cp = a.bytes(std::max<size_t>(w.cp_bytes, 16));
+  w.cp = g.one_order ? nullptr : a.bytes(std::max<size_t>(w.cp_bytes, 16));
   return w;
 }
 
@@ -454,11 +454,11 @@ static DWsF d_carve_f(const DBlock& d, Arena& a) {
   const int64_t rc[3][2] = {{d.cout, 9LL * d.cin}, {d.cout, 9LL * d.cout}, {d.cout, d.cin}};
   w.sn = a.bytes(sn_group_ws(rc, d.lsc ? 3 : 2));
   w.skip = d.lsc ? a.f32((size_t)d.B * d.Ho * d.Wo * d.Cop) : nullptr;
-  w.cp_bytes = d.f32 ? 0 : std::max({conv_split_ws(G_DIRECT, d.B, d.H, d.W, d.im2col ? 1 : 3, d.Cip, d.Cop),
+  w.cp_bytes = d.f32 || d.one_order ? 0 : std::max({conv_split_ws(G_DIRECT, d.B, d.H, d.W, d.im2col ? 1 : 3, d.Cip, d.Cop),
                                      conv_split_ws(G_DIRECT, d.B, d.Ho, d.Wo, 1, d.Cip, d.Cop),
                                      d.s2conv() ? conv_split_ws(G_S2, d.B, d.Ho, d.Wo, 4, d.Cop, d.Cop)
                                                 : conv_split_ws(G_DIRECT, d.B, d.H, d.W, 3, d.Cop, d.Cop)});
-  w.cp = a.bytes(std::max<size_t>(w.cp_bytes, 16));
+  w.cp = d.one_order ? nullptr : a.bytes(std::max<size_t>(w.cp_bytes, 16));
   return w;
 }
 
@@ -475,20 +475,20 @@ static DWsB d_carve_b(const DBlock& d, Arena& a, int n_cu) {
   w.dwpsc = d.lsc ? a.f32((size_t)d.Cop * d.Cip) : nullptr;
   // the pooled conv2's gradient in its stride-2 4x4 form, folded to 3x3 after
   w.dwp2s = d.s2conv() ? a.f32((size_t)d.Cop * 16 * d.Cop) : nullptr;
-  w.wg_bytes = std::max(conv_wgrad_ws(d.f32, M, 3, d.Cip, d.Cop, n_cu), conv_wgrad_ws(d.f32, M, 3, d.Cop, d.Cop, n_cu));
-  if (d.s2conv()) w.wg_bytes = std::max(w.wg_bytes, conv_wgrad_ws(d.f32, Mo, 4, d.Cop, d.Cop, n_cu));
-  if (d.lsc) w.wg_bytes = std::max(w.wg_bytes, conv_wgrad_ws(d.f32, Mo, 1, d.Cip, d.Cop, n_cu));
+  w.wg_bytes = std::max(conv_wgrad_ws(d.f32, M, 3, d.Cip, d.Cop, n_cu, d.one_order), conv_wgrad_ws(d.f32, M, 3, d.Cop, d.Cop, n_cu, d.one_order));
+  if (d.s2conv()) w.wg_bytes = std::max(w.wg_bytes, conv_wgrad_ws(d.f32, Mo, 4, d.Cop, d.Cop, n_cu, d.one_order));
+  if (d.lsc) w.wg_bytes = std::max(w.wg_bytes, conv_wgrad_ws(d.f32, Mo, 1, d.Cip, d.Cop, n_cu, d.one_order));
   w.wg = a.bytes(w.wg_bytes);
   w.cs = a.bytes(colsum_ws_bytes(M, d.Cop));
   w.dh = a.bytes((size_t)M * d.Cop * e);
   w.dxs = d.lsc ? a.f32((size_t)Mo * d.Cip) : nullptr;
   w.part = a.f32((size_t)kSnbParts * kSnGroupMax);
   w.dcol = d.im2col ? a.f32((size_t)M * d.Cip) : nullptr;
-  w.cp_bytes = d.f32 ? 0 : std::max({d.subdgrad() ? conv_split_ws(G_SUB, d.B, d.Ho, d.Wo, 2, d.Cop, d.Cop)
+  w.cp_bytes = d.f32 || d.one_order ? 0 : std::max({d.subdgrad() ? conv_split_ws(G_SUB, d.B, d.Ho, d.Wo, 2, d.Cop, d.Cop)
                                                   : conv_split_ws(G_DIRECT, d.B, d.H, d.W, 3, d.Cop, d.Cop),
                                      conv_split_ws(G_DIRECT, d.B, d.Ho, d.Wo, 1, d.Cop, d.Cip),
                                      conv_split_ws(G_DIRECT, d.B, d.H, d.W, d.im2col ? 1 : 3, d.Cop, d.Cip)});
-  w.cp = a.bytes(std::max<size_t>(w.cp_bytes, 16));
+  w.cp = d.one_order ? nullptr : a.bytes(std::max<size_t>(w.cp_bytes, 16));
   return w;
 }
 
@@ -548,7 +548,6 @@ void DBlock::prep(hipStream_t st, const Params& P, void* sn_ws, bool for_bwd) {
 void DBlock::fwd(const Exec& ex, const Params& P, const void* x, void* y) {
   Arena a(ex.ws);
   DWsF w = d_carve_f(*this, a);
-  if (ex.one_order) w.cp = nullptr;
   if (!prepped) prep(ex.st, P, w.sn);
   const int R1 = im2col ? 1 : 3, K1 = im2col ? 9 * cin : cin, ksc = im2col ? 4 * cin : 0;
   // h = conv3x3([relu](x)) + b1
@@ -592,7 +591,6 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
                  bool wgrad) {
   Arena a(ex.ws);
   DWsB w = d_carve_b(*this, a, ex.n_cu);
-  if (ex.one_order) w.cp = nullptr;
   const int64_t M = (int64_t)B * H * W, Mo = (int64_t)B * Ho * Wo;
   const int R1 = im2col ? 1 : 3, K1 = im2col ? 9 * cin : cin, ksc = im2col ? 4 * cin : 0;
   // the data-gradient weights: packed by prep, or here
@@ -620,13 +618,13 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
       g2s.g = dy; g2s.Hs = Ho; g2s.Ws = Wo; g2s.C = Cop;
       ConvIn a2s = a2;
       a2s.gather = G_S2;
-      conv_wgrad(sw, f32, g2s, a2s, Ho, Wo, 4, Cop, w.dwp2s, w.wg, w.wg_bytes, ex.n_cu);
+      conv_wgrad(sw, f32, g2s, a2s, Ho, Wo, 4, Cop, w.dwp2s, w.wg, w.wg_bytes, ex.n_cu, one_order);
       fold_pool4_wgrad(sw, w.dwp2s, Cop, Cop, w.dwp2);
     } else {
-      conv_wgrad(sw, f32, g2, a2, H, W, 3, Cop, w.dwp2, w.wg, w.wg_bytes, ex.n_cu);
+      conv_wgrad(sw, f32, g2, a2, H, W, 3, Cop, w.dwp2, w.wg, w.wg_bytes, ex.n_cu, one_order);
     }
     // both biases add to the block output (after the pool): the same column sum of dy
-    colsum(sw, f32, dy, Mo, cout, Cop, 1.f, P.gr("conv2.b"), w.cs, lsc ? P.gr("sc.b") : nullptr);
+    colsum(sw, f32, dy, Mo, cout, Cop, 1.f, P.gr("conv2.b"), w.cs, lsc ? P.gr("sc.b") : nullptr, one_order);
   }
   // dh = (conv2^T dc2) * [h > 0]
   ConvIn d2;
@@ -649,8 +647,8 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
   a1.x = x; a1.B = B; a1.Hx = H; a1.Wx = W; a1.C = Cip; a1.relu = preact; a1.c_real = K1;
   if (wgrad) {
     side.fork();   // dh is ready
-    conv_wgrad(sw, f32, g1, a1, H, W, R1, Cop, w.dwp1, w.wg, w.wg_bytes, ex.n_cu);
-    colsum(sw, f32, w.dh, M, cout, Cop, 1.f, P.gr("conv1.b"), w.cs);
+    conv_wgrad(sw, f32, g1, a1, H, W, R1, Cop, w.dwp1, w.wg, w.wg_bytes, ex.n_cu, one_order);
+    colsum(sw, f32, w.dh, M, cout, Cop, 1.f, P.gr("conv1.b"), w.cs, nullptr, one_order);
   }
   // skip
   if (lsc) {
@@ -659,7 +657,7 @@ void DBlock::bwd(const Exec& ex, const Params& P, const void* x, const void* dy,
     ConvIn as;
     as.x = x; as.B = B; as.Hx = H; as.Wx = W; as.C = Cip; as.c_real = cin;
     if (down) { as.x = xp; as.Hx = Ho; as.Wx = Wo; }
-    if (wgrad) conv_wgrad(sw, f32, gs, as, Ho, Wo, 1, Cop, w.dwpsc, w.wg, w.wg_bytes, ex.n_cu);
+    if (wgrad) conv_wgrad(sw, f32, gs, as, Ho, Wo, 1, Cop, w.dwpsc, w.wg, w.wg_bytes, ex.n_cu, one_order);
     if (dx) {
       ConvIn ds;
       ds.x = dy; ds.B = B; ds.Hx = Ho; ds.Wx = Wo; ds.C = Cop;

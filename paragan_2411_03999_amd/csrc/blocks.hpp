@@ -85,16 +85,18 @@ struct Exec {
   // join: side -> st); both streams are joined when the call returns
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  // a D block's convolutions sum in one order whatever the batch: nothing in
-  // the discriminator couples the batch, so in a network its activations and
-  // activation gradients are the same bits at any batch
-  bool one_order = false;
 };
 
 // ----------------------------------------------------------- G block
+// one_order (set before plan_saved; a network sets it): the sums that later
+// ReLU, max-pool and hinge decisions of a training iteration hang on keep an
+// order set by fixed rules on the sizes and not by the launch plans -- G's
+// activations; D's activations, their gradients and its weight gradients.
+// (Three updates of a deep bf16 network carry a last-bit difference of an
+// early sum into several percent of the later losses and SN vectors.)
 struct GBlock {
   int B, H, W, cin, cout, dc, npi;
-  bool f32;
+  bool f32, one_order = false;
   float bn_eps, sn_eps;
   int Cip, Cop;
   // saved by fwd for bwd
@@ -129,7 +131,7 @@ struct GBlock {
 // ----------------------------------------------------------- D block
 struct DBlock {
   int B, H, W, cin, cout, npi;
-  bool preact, down, lsc, f32;
+  bool preact, down, lsc, f32, one_order = false;   // one_order: as in GBlock
   // the input is an image in 3x3-patch form (img_to_im2col, 9 cin <= 32
   // channels): conv1 runs as a 1x1 conv over the patches, the skip reads
   // the centre tap, and dx is the fp32 image gradient [B][H][W][4]
@@ -167,6 +169,7 @@ struct DBlock {
 // ----------------------------------------------------------- attention
 struct Attn {
   int B, H, W, C, npi;
+  bool one_order = false;    // as in GBlock (its activations always are)
   float sn_eps;
   int Cp, dk, dv, Nqkv;      // padded head dims; Nqkv = 2*dk + dv
   SNSlot sn[4];

@@ -945,20 +945,20 @@ static void wgrad_plan(bool f32, int64_t M, int R, int Cin, int Np, int n_cu,
   if (splits < 1) splits = 1;
 }
 
-size_t conv_wgrad_ws(bool f32, int64_t M, int R, int Cin, int Np, int n_cu) {
+size_t conv_wgrad_ws(bool f32, int64_t M, int R, int Cin, int Np, int n_cu, bool one_order) {
   int tn, tk, sp;
   int64_t mps;
   wgrad_plan(f32, M, R, Cin, Np, n_cu, tn, tk, sp, mps);
   const size_t legacy = sp > 1 ? align256((size_t)sp * Np * R * R * Cin * 4) : 0;
-  return f32 ? legacy : std::max(legacy, wgrad_tr_ws(M, R, Cin, Np, n_cu));
+  return f32 ? legacy : std::max(legacy, wgrad_tr_ws(M, R, Cin, Np, n_cu, one_order));
 }
 
 void conv_wgrad(hipStream_t s, bool f32, const GradIn& g, const ConvIn& in, int H, int W,
-                int R, int Np, float* dw, void* ws, size_t ws_bytes, int n_cu) {
+                int R, int Np, float* dw, void* ws, size_t ws_bytes, int n_cu, bool one_order) {
   const double flops =
       2.0 * (double)in.B * H * W * (g.n_real ? g.n_real : Np) * R * R * (in.c_real ? in.c_real : in.C);
   if (!f32 && wgrad_tr_ok(g, in, H, W, R, Np)) {
-    if ((int64_t)in.B * H * W > 0) wgrad_tr(s, g, in, H, W, R, Np, dw, ws, ws_bytes, n_cu, flops);
+    if ((int64_t)in.B * H * W > 0) wgrad_tr(s, g, in, H, W, R, Np, dw, ws, ws_bytes, n_cu, one_order, flops);
     return;
   }
   WgK k;

@@ -814,13 +814,31 @@ constexpr CfTile kCfTiles[] = {
 // the 1536-channel 3x3 conv at 1024 pixels (432 steps): 191 us unsplit on 48
 // 128 x 256 tiles, 57 + 8 us in five splits.
 //
-// one_order: the order in which an output's K products are summed must not
-// depend on the number of images: no split, and the kernel family (halo:
-// chunks outside taps; ring: taps outside channels) from the image's and
-// the filter's shape alone -- except that direct 3x3 filters of 256 n
-// channels that are no multiple of 192 take the halo kernel only from 192
-// tiles on (its 256 x 256 tile is the one that fits them well).
+// one_order (networks' activations, on whose last bits later decisions hang):
+// no split, and the kernel family, which sets the order of an output's sums
+// (halo: chunks outside taps; ring: taps outside channels), by halo_family's
+// rule and not by the model; every tile of a family sums alike, so the model
+// picks among them.
 constexpr int kCUs = 256, kSplitSteps = 8;
+
+// Whether a conv that must keep its sums' order takes a halo kernel: where
+// 256 x 256 tiles come in whole rounds over the CUs (the last at least three
+// quarters full) only if the direct patch fits that tile, else for multiples
+// of 192 channels and for 96 where the patch fits.  (The rule is part of the
+// results: it decides the last bits, so it stays as it is whatever the tiles
+// cost.)
+bool halo_family(int hk, int64_t M, int H, int W, int C, int Np) {
+  if (hk == kRing) return false;
+  auto fits = [&](int bm, int ppx) {
+    const int np = halo_patch(bm, H, W);
+    return np > 0 && np <= ppx;
+  };
+  const int64_t t8 = cdiv(M, 256) * (Np / 256) * (hk == kHaloSub ? 4 : 1);
+  if (Np % 256 == 0 && t8 >= 192 && (t8 % 256 == 0 || t8 % 256 >= 192)) return hk == kHaloDirect && fits(256, 384);
+  if (Np % 192 == 0 && (hk != kHaloSub || C >= 192) && fits(128, 320)) return true;
+  return Np == 96 && (hk == kHaloDirect ? fits(512, 896) : fits(256, 448));
+}
+
 CfPlan cf_plan(int gather, int64_t M, int H, int W, int R, int C, int Np, bool one_order) {
   const int par = gather == G_SUB ? 4 : 1;
   const int hk = gather == G_DIRECT && R == 3 ? kHaloDirect
@@ -829,18 +847,15 @@ CfPlan cf_plan(int gather, int64_t M, int H, int W, int R, int C, int Np, bool o
                                               : kRing;
   CfPlan best{};
   double best_t = 1e300;
+  const bool family = one_order && halo_family(hk, M, H, W, C, Np);
   bool halo = false;
   for (const CfTile& t : kCfTiles) {   // (halo tiles first)
+    if (one_order && (t.kernel != kRing) != family) continue;
     if (t.kernel != kRing) {
       const int np = t.kernel == hk ? halo_patch(t.bm, H, W) : 0;
       if (np <= 0 || np > t.ppx) continue;
-      if (one_order) {
-        const bool suits = t.kernel == kHaloSub && C < 192 ? Np == 96 : Np % 192 == 0 || Np == 96;
-        if (!suits && (t.kernel != kHaloDirect || t.bn != 256 || Np % 256 != 0 || cdiv(M, 256) * (Np / 256) < 192))
-          continue;
-      }
       halo = true;
-    } else if ((one_order && halo) || (t.bm == 256 && t.bn <= 64 && Np > t.bn)) {
+    } else if (t.bm == 256 && t.bn <= 64 && Np > t.bn) {
       continue;
     }
     CfPlan p{};

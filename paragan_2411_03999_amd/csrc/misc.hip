@@ -965,18 +965,18 @@ __global__ __launch_bounds__(1024) void k_colsum_fin(const float* part, int nch,
   }
 }
 
-size_t colsum_ws_bytes(int64_t M, int C) {
+size_t colsum_ws_bytes(int64_t M, int C) {   // (one_order needs no more chunks)
   return align256((size_t)cdiv(M, red_shape(C, M, false).rows_blk) * C * 4);
 }
 
 void colsum(hipStream_t st, bool f32, const void* x, int64_t M, int C, int ldc, float scale, float* out,
-            void* ws, float* out2) {
+            void* ws, float* out2, bool one_order) {
   if (M <= 0) {
     fill(st, out, C, 0.f);
     if (out2) fill(st, out2, C, 0.f);
     return;
   }
-  const RedShape sh = red_shape(C, M, false);
+  const RedShape sh = red_shape(C, M, one_order);
   PG_CHECK(ldc >= cpad(C) && ldc % 8 == 0, "colsum: channel stride");
   const int nch = (int)cdiv(M, sh.rows_blk);
   float* part = (float*)ws;

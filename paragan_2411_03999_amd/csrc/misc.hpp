@@ -80,10 +80,11 @@ void sn_bwd(hipStream_t st, const float* dwp, const float* W, const float* u, co
             const float* sigma, int Cout, int Cin, int R, int Cp, const float* scale, float* dW,
             float* part);
 
-// out[c] = scale * sum_m x[m][c] (and out2[c], unless null)
+// out[c] = scale * sum_m x[m][c] (and out2[c], unless null).  one_order: the
+// chunks of a sum at 32 rows per thread whatever the size
 size_t colsum_ws_bytes(int64_t M, int C);
 void colsum(hipStream_t st, bool f32, const void* x, int64_t M, int C, int ldc, float scale, float* out,
-            void* ws, float* out2 = nullptr);
+            void* ws, float* out2 = nullptr, bool one_order = false);
 
 // batch norm
 size_t bn_stats_ws_bytes(int64_t M, int C);

@@ -141,7 +141,7 @@ void GNet::plan_saved(Arena& s) {
     GBlock g;
     g.B = B_; g.H = res; g.W = res; g.cin = a.g_mult[i] * a.ch; g.cout = a.g_mult[i + 1] * a.ch;
     g.dc = a.dc; g.npi = a.npi; g.f32 = false; g.bn_eps = a.bn_eps; g.sn_eps = a.sn_eps;
-    g.keep_dgrad = true;
+    g.keep_dgrad = g.one_order = true;
     g.plan_saved(s);
     blocks_.push_back(g);
     res *= 2;
@@ -357,6 +357,7 @@ void DNet::plan_saved(Arena& s) {
     b.B = N_; b.H = sp.H; b.W = sp.W; b.cin = sp.cin; b.cout = sp.cout; b.npi = a.npi;
     b.preact = sp.preact; b.down = sp.down; b.lsc = sp.lsc; b.f32 = false; b.sn_eps = a.sn_eps;
     b.im2col = j == 0;   // the image enters as 3x3 patches
+    b.one_order = true;
     b.keep_dgrad = true;
     b.plan_saved(s);
     blocks_.push_back(b);
@@ -364,6 +365,7 @@ void DNet::plan_saved(Arena& s) {
     if (sp.attn) {
       attn_after_ = j;
       attn_.B = N_; attn_.H = b.Ho; attn_.W = b.Wo; attn_.C = sp.cout; attn_.npi = a.npi; attn_.sn_eps = a.sn_eps;
+      attn_.one_order = true;
       attn_.plan_saved(s);
       attn_out_ = s.bytes((size_t)N_ * b.Ho * b.Wo * cpad(sp.cout) * 2);
     }
@@ -435,7 +437,6 @@ void DNet::fwd(const Exec& ex, const Params& P, const float* x, const int32_t* y
   Arena w(ex.ws);
   DNetWs r = dnet_carve(a, N_, blocks_, attn_after_ >= 0 ? &attn_ : nullptr, w, ex.n_cu);
   Exec eb{ex.st, ex.n_cu, r.blk, r.blk_bytes};
-  eb.one_order = true;
   img_to_im2col(ex.st, x, N_, a.img, a.img, act_[0]);
   const void* h = act_[0];
   for (int j = 0; j < (int)blocks_.size(); ++j) {
@@ -461,7 +462,7 @@ void DNet::bwd(const Exec& ex, const Params& P, const int32_t* y, const float* d
   const Arch& a = a_;
   Arena w(ex.ws);
   DNetWs r = dnet_carve(a, N_, blocks_, attn_after_ >= 0 ? &attn_ : nullptr, w, ex.n_cu);
-  Exec eb{ex.st, ex.n_cu, r.blk, r.blk_bytes, ex.side, ex.ev_fork, ex.ev_join, true};
+  Exec eb{ex.st, ex.n_cu, r.blk, r.blk_bytes, ex.side, ex.ev_fork, ex.ev_join};
   const DBlock& last = blocks_.back();
   const int nb = (int)blocks_.size();
   const void* xl = in_[nb];

@@ -63,8 +63,9 @@ struct ConvOut {
 // w: packed [Np][R][R][in.C] in the activation type (bf16 or fp32).
 // part (conv_split_ws bytes, 16-byte aligned): scratch for the fp32 partials
 // of a conv whose K loop is split over blocks.  With part == nullptr the
-// conv is not split and sums an output's products in an order that does not
-// depend on the batch.
+// conv is not split and sums an output's products in one of two orders (taps
+// outside channels, or chunks of 32 channels outside taps), chosen by a fixed
+// rule on the sizes, the batch among them, and not by the launch plan.
 void conv_fwd(hipStream_t s, bool f32, const ConvIn& in, int H, int W, int R,
               const void* w, int Np, const ConvOut& out, void* part = nullptr, size_t part_bytes = 0);
 // bf16 only (0 for a conv that is not split)
@@ -88,10 +89,12 @@ struct GradIn {
 
 // dw[n][r][s][c] = gscale * sum_m g[m][n] * A[m][(r,s,c)], A = im2col(in).
 // dw: fp32 [Np][R][R][in.C] (padded).  ws: scratch for split-M partials.
-size_t conv_wgrad_ws(bool f32, int64_t M, int R, int Cin, int Np, int n_cu);
+// one_order (bf16): the splits of the pixel range by a fixed rule and not by
+// the launch plan, for a gradient whose update feeds later decisions.
+size_t conv_wgrad_ws(bool f32, int64_t M, int R, int Cin, int Np, int n_cu, bool one_order = false);
 void conv_wgrad(hipStream_t s, bool f32, const GradIn& g, const ConvIn& in,
                 int H, int W, int R, int Np, float* dw, void* ws, size_t ws_bytes,
-                int n_cu);
+                int n_cu, bool one_order = false);
 
 // bf16 weight gradient through LDS transpose reads (wgrad.hip), for direct or
 // upsampled operands without a BN-affine prologue.  wgrad_tr_ok tells whether
@@ -107,8 +110,8 @@ bool wgrad_sub_ok(const GradIn& g, const ConvIn& in, int Np);
 size_t wgrad_sub_ws(int64_t Msrc, int Cin, int Np, int n_cu);
 void wgrad_sub(hipStream_t s, const GradIn& g, const ConvIn& in, int Np, float* dw, void* ws, size_t ws_bytes,
                int n_cu);
-size_t wgrad_tr_ws(int64_t M, int R, int Cin, int Np, int n_cu);
+size_t wgrad_tr_ws(int64_t M, int R, int Cin, int Np, int n_cu, bool one_order);
 void wgrad_tr(hipStream_t s, const GradIn& g, const ConvIn& in, int H, int W, int R, int Np, float* dw,
-              void* ws, size_t ws_bytes, int n_cu, double flops);
+              void* ws, size_t ws_bytes, int n_cu, bool one_order, double flops);
 
 }  // namespace pg

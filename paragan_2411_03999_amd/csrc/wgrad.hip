@@ -545,7 +545,7 @@ constexpr TrCfg kTrCfgs[] = {{2, 2, 4, 2, 0.82f, 1.19f}, {2, 2, 2, 4, 0.89f, 1.2
                              {1, 4, 3, 2, 0.84f, 1.12f}, {1, 4, 3, 3, 1.10f, 1.59f}, {2, 2, 2, 2, 0.64f, 0.75f},
                              {4, 2, 2, 4, 1.08f, 1.10f},
                              {4, 2, 2, 3, 0.82f, 0.82f}, {2, 2, 3, 3, 0.79f, 1.05f}};
-constexpr int kRow256 = 7, kRow192 = 8, kTrCount = 9;
+constexpr int kTr256 = 6, kRow256 = 7, kRow192 = 8, kTrCount = 9;
 
 struct TrPlan {
   int cfg, tiles_n, tiles_k, splits, m_per_split;
@@ -567,8 +567,13 @@ bool row3_shape(int R, int Cin, int Np) {
 // 617 us.  1x1 filters on 32 blocks of 32 stages: 40 us, on 216: 20.)
 // row3: the row-tap kernel is a candidate.  classes: parity classes of the
 // sub-pixel form, which share the launch.
-TrPlan tr_plan(int64_t M, int R, int Cin, int Np, int n_cu, bool row3, int classes) {
+// one_order: the splits, which set the order of a result's sums, are
+// fixed_splits' and only the tile is the model's (within a split every tile
+// adds the pixels alike).
+int64_t fixed_splits(int64_t M, int64_t K, int Np, int n_cu);
+TrPlan tr_plan(int64_t M, int R, int Cin, int Np, int n_cu, bool row3, int classes, bool one_order) {
   const int64_t K = (int64_t)R * R * Cin, nout = (int64_t)Np * K;
+  const int64_t fixed = one_order ? fixed_splits(M, K, Np, n_cu) : 0;
   const int64_t smax = std::max<int64_t>(1, std::min<int64_t>(M / (2 * kMS), (512LL << 20) / (4 * nout)));
   TrPlan best{0, 0, 0, 1, 0};
   double best_t = 1e300;
@@ -579,11 +584,11 @@ TrPlan tr_plan(int64_t M, int R, int Cin, int Np, int n_cu, bool row3, int class
     const int tk = c >= kRow256 ? 3 * (Cin / 64) : (int)cdiv(K, t.WN * t.TN * 32);
     const bool wide = t.WM * t.WN == 8;
     const int64_t tiles = (int64_t)tn * tk * classes, cap = (int64_t)n_cu * (wide ? 1 : 2);
-    for (int q = 0; q <= 6; ++q) {
+    for (int q = 0; q <= (fixed ? 0 : 6); ++q) {
       // one split; a block on every CU; then 1, 2, 3, 4, 6 full rounds
       static const int kHalves[] = {0, 1, 2, 4, 6, 8, 12};
       int64_t s = q == 0 ? 1 : kHalves[q] * cap / 2 / tiles;
-      s = std::max<int64_t>(1, std::min(s, smax));
+      s = fixed ? fixed : std::max<int64_t>(1, std::min(s, smax));
       const int64_t mps = cdiv(cdiv(M, s), kMS) * kMS;
       s = cdiv(M, mps);
       const int64_t full = tiles * s / cap, rem = tiles * s % cap;
@@ -597,6 +602,43 @@ TrPlan tr_plan(int64_t M, int R, int Cin, int Np, int n_cu, bool row3, int class
     }
   }
   return best;
+}
+
+// The split count that one_order keeps (the rule is part of the results): of
+// the four-wave tiles and 256 x 256 the one with the least padded work, 256 x
+// 256 where both dimensions are its multiples; splits of at least 1024 pixels
+// that give the chip four blocks of that tile per CU, and for 256 x 256 one
+// to two, as many as fill the last round best.
+int64_t fixed_splits(int64_t M, int64_t K, int Np, int n_cu) {
+  int cfg = 0;
+  double best = 1e300;
+  for (int c = 0; c <= kTr256; ++c) {
+    const TrCfg& t = kTrCfgs[c];
+    const int bn = t.WM * t.TM * 32, bk = t.WN * t.TN * 32;
+    const double eff = t.TM * t.TN >= 8 ? 1.0 : (t.TM * t.TN >= 6 ? 0.92 : 0.8);
+    const double cost = (double)cdiv(Np, bn) * cdiv(K, bk) * bn * bk / eff;
+    if (cost < best * 0.999) {
+      best = cost;
+      cfg = c;
+    }
+  }
+  if (Np % 256 == 0 && K % 256 == 0) cfg = kTr256;
+  const TrCfg& t = kTrCfgs[cfg];
+  const int64_t tiles = cdiv(Np, t.WM * t.TM * 32) * cdiv(K, t.WN * t.TN * 32);
+  const int64_t most = std::min<int64_t>(std::max<int64_t>(1, M / 1024), (512LL << 20) / (4 * (int64_t)Np * K));
+  if (cfg != kTr256) return std::max<int64_t>(1, std::min(cdiv(4LL * n_cu, tiles), most));
+  const int64_t s0 = std::max<int64_t>(1, std::min(cdiv((int64_t)n_cu, tiles), most));
+  int64_t sp = s0;
+  double best_fill = 0.0;
+  for (int64_t c = s0; c <= std::min(2 * s0, most); ++c) {
+    const int64_t b = c * tiles;
+    const double fill = (double)b / (double)(cdiv(b, (int64_t)n_cu) * n_cu);
+    if (fill > best_fill + 1e-9) {
+      best_fill = fill;
+      sp = c;
+    }
+  }
+  return sp;
 }
 
 template <int WM, int WN, int TM, int TN>
@@ -662,14 +704,14 @@ bool wgrad_tr_ok(const GradIn& g, const ConvIn& in, int H, int W, int R, int Np)
 }
 
 // (whether the row-tap kernel can run depends on the image too: room for either plan)
-size_t wgrad_tr_ws(int64_t M, int R, int Cin, int Np, int n_cu) {
-  int sp = tr_plan(M, R, Cin, Np, n_cu, false, 1).splits;
-  if (row3_shape(R, Cin, Np)) sp = std::max(sp, tr_plan(M, R, Cin, Np, n_cu, true, 1).splits);
+size_t wgrad_tr_ws(int64_t M, int R, int Cin, int Np, int n_cu, bool one_order) {
+  int sp = tr_plan(M, R, Cin, Np, n_cu, false, 1, one_order).splits;
+  if (row3_shape(R, Cin, Np)) sp = std::max(sp, tr_plan(M, R, Cin, Np, n_cu, true, 1, one_order).splits);
   return sp > 1 ? align256((size_t)sp * Np * R * R * Cin * 4) : 0;
 }
 
 void wgrad_tr(hipStream_t s, const GradIn& g, const ConvIn& in, int H, int W, int R, int Np, float* dw,
-              void* ws, size_t ws_bytes, int n_cu, double flops) {
+              void* ws, size_t ws_bytes, int n_cu, bool one_order, double flops) {
   WgTrK k;
   k.g = (const bf16_t*)g.g;
   k.x = (const bf16_t*)in.x;
@@ -695,7 +737,7 @@ void wgrad_tr(hipStream_t s, const GradIn& g, const ConvIn& in, int H, int W, in
   // the row-tap form (k_wgrad_row3): a direct 3x3 conv over images whose
   // rows are whole 32-pixel stages
   const bool row3 = row3_shape(R, in.C, Np) && in.gather == G_DIRECT && W % 32 == 0;
-  const TrPlan p = tr_plan(k.M, R, in.C, Np, n_cu, row3, 1);
+  const TrPlan p = tr_plan(k.M, R, in.C, Np, n_cu, row3, 1, one_order);
   k.m_per_split = p.m_per_split;
   k.tiles_n = p.tiles_n;
   k.tiles_k = p.tiles_k;
@@ -740,7 +782,7 @@ void wgrad_tr(hipStream_t s, const GradIn& g, const ConvIn& in, int H, int W, in
 // and dW_ab = sum over the class's pixels of dY (x) (the 2x2 window of the
 // source): 4/9 of the upsampled form's MACs, on the unexpanded source.
 static TrPlan sub_plan(int64_t Msrc, int Cin, int Np, int n_cu) {
-  return tr_plan(Msrc, 2, Cin, Np, n_cu, false, 4);   // four parity classes share the CUs
+  return tr_plan(Msrc, 2, Cin, Np, n_cu, false, 4, false);   // four parity classes share the CUs
 }
 
 size_t wgrad_sub_ws(int64_t Msrc, int Cin, int Np, int n_cu) {

@@ -2,23 +2,29 @@
 
 A ReLU (max-pool, hinge) input within rounding of zero turns with the last
 bit of the sums before it, and one turned element moves a small block's
-gradients by 1e-3 and a training step's later losses by more.  So a
-rearrangement that is meant to save time only must leave those sums' bits
-alone.  An fp32 block's convolutions add an output's products one by one, tap by tap
-and channel by channel, whichever kernel its size selects, and its batch
-statistics have one chunking.  The pins are digests of whole outputs at seeded inputs.  The fp32 matrix
-instruction adds its products in K order with one rounding each, so nothing
-but the order of operations enters them."""
+gradients by 1e-3 and a training iteration's later losses and SN vectors by
+several percent.  So a rearrangement that is meant to save time only must
+leave those sums' bits alone:
+* an fp32 block's convolutions add an output's products one by one, tap by
+  tap and channel by channel, whichever kernel its size selects, and its
+  batch statistics have one chunking;
+* in a network, G's activations, D's activations and D's gradients follow
+  fixed rules on the sizes, not the launch plans.
+The pins are digests of whole outputs at seeded inputs: a change here is a
+change of the order of operations (or of a rule above), to be made knowingly
+and with a new pin."""
 import hashlib
 
 import numpy as np
 import pytest
 
+from oracle import biggan as O
 from oracle import blocks as OB
 from paragan_2411_03999_amd import lib
 from paragan_2411_03999_amd.synth import Stream, init_params, init_u
 
 from .parity import SEEN, context, harvest, need_gpu
+from .test_gpu_train_step import hparams, make_nets, run_train_step, step_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -102,3 +108,32 @@ def test_f32_gblock_forward_bits(shape):
     torch.cuda.synchronize()
     harvest(ctx)
     assert digest(Y) == F32_PINS[shape]
+
+
+# ---------------------------------------------------------------- networks
+# (arch, B, n_D): digests of a sample, and of an iteration's losses, D's
+# parameters and both networks' SN vectors
+NET_PINS = {
+    ("biggan128", 8, 2): ("c9ac48b712c3b841", "6f449da94aab6cb1"),
+    ("biggan512", 2, 1): ("cb63291edb0b7d8a", "770ba2ccecea7362"),
+}
+
+
+@pytest.mark.parametrize("key", list(NET_PINS))
+def test_network_bits(key):
+    torch = need_gpu()
+    arch, B, n_D = key
+    a = {"biggan128": O.biggan128, "biggan512": O.biggan512}[arch]()
+    d, s, _, _, G, D = make_nets(torch, a, B, 813, hparams())
+    inp, keep = step_inputs(torch, s, a, B, n_D)
+    ctx = context()
+    ws = lib.workspace(lib.paragan_train_step_ws_size(d))
+    img = torch.empty((B, a.img, a.img, 3), dtype=torch.float32, device="cuda")
+    ctx.check(lib.paragan_g_sample(ctx, d, G.clone(torch).state, keep[2 * n_D], keep[3 * n_D], img, ws))
+    torch.cuda.synchronize()
+    sample = digest(img)
+    losses = torch.tensor(run_train_step(torch, d, G, D, inp, n_D, ws, ctx))
+    harvest(ctx)
+    got = (sample, digest(losses, D.P, D.U, G.U))
+    print(key, got, flush=True)
+    assert got == NET_PINS[key]
