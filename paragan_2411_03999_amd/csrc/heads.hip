@@ -124,10 +124,34 @@ void im2col_grad(hipStream_t st, const float* dcol, int N, int H, int W, float* 
 // keeps full precision).  The 27 filter columns n = co * 9 + r * 3 + s (27 of
 // a 32-wide tile) are the N side of both products; the 3x3 window turns into
 // 9-term gathers around them.
-// output rows per forward block: 16, or 8 where that leaves less than 512
-// blocks (two per CU hide each other's row steps; the two extra Z rows of a
-// block cost 1/8 more products)
-static int ghead_rows(int B, int H, int ncb) { return (int64_t)B * cdiv(H, 16) * ncb >= 512 ? 16 : 8; }
+// Rows of one image per block, for each of the layer's kernels, by modelled
+// time: a block costs its rows and about two more (halo rows, staging, its
+// partial sums and their addition); blocks run in rounds of two per CU, and a
+// last round of at most one per CU takes `alone` halves of a full one (alone,
+// a forward or weight-gradient block waits for its own barriers).  Swept over
+// 80 layers of 1 to 256 images, 16 to 512 rows and columns, 24 to 128
+// channels, at 1 to 16 rows a block: the choice is within a few us of the best
+// there.  (32 x 128 x 128 x 96 forward: 256 blocks of 16 rows 63 us, 512 of 8
+// 57; 44 x 145 x 52 x 88: 440 of 16 82, 836 of 8 91.  Weight gradient of the
+// former: 256 blocks 79, 512 58.  The whole layer at 37 x 22 x 16 x 104, rows
+// of both backward kernels: 814 blocks of one row 170 us, 222 of four 115; at
+// 19 x 112 x 68 x 80, the batch-norm passes: 266 blocks of 8 rows 211, 228 of
+// ten 183.)
+static double ghead_time(int64_t blocks, int rows, double alone) {
+  const int64_t rem = blocks % 512;
+  return (2.0 * (blocks / 512) + (rem == 0 ? 0.0 : rem <= 256 ? alone : 2.0)) * (rows + 2);
+}
+static int ghead_best_rows(int B, int H, int most, double alone) {
+  int rows = 1;
+  for (int r = 2; r <= most; ++r)   // (ties: fewer blocks)
+    if (ghead_time((int64_t)B * cdiv(H, r), r, alone) <= ghead_time((int64_t)B * cdiv(H, rows), rows, alone)) rows = r;
+  return rows;
+}
+// output rows per forward block
+static int ghead_rows(int B, int H, int ncb) {
+  auto time = [&](int r) { return ghead_time((int64_t)B * cdiv(H, r) * ncb, r, 1.2); };
+  return time(8) < time(16) ? 8 : 16;
+}
 constexpr int kZS = 33;     // LDS floats per Z position (odd: conflict-free gathers)
 constexpr int kZP = 130;    // Z positions per ring row: 128 output columns + 2 halo
 
@@ -306,11 +330,10 @@ constexpr size_t kBnbLds = 64 * 1024;
 static size_t ghead_bnb_lds_at(int tr, int W, int Cp) {
   return ((size_t)(tr + 2) * (W + 2) * 3 + 3) / 4 * 16 + (8 + 6) * (size_t)Cp * 4;
 }
-// rows per block: up to 8, fewer while that leaves less than 512 blocks or does not fit in LDS
 static int ghead_bnb_rows(int B, int H, int W, int Cp) {
-  int tr = (int)std::max<int64_t>(1, std::min<int64_t>(8, (int64_t)B * H / 512));
-  while (tr > 1 && ghead_bnb_lds_at(tr, W, Cp) > kBnbLds) --tr;
-  return tr;
+  int most = 16;
+  while (most > 1 && ghead_bnb_lds_at(most, W, Cp) > kBnbLds) --most;
+  return ghead_best_rows(B, H, most, 1.0);
 }
 
 constexpr int bnb_groups(int ct) { return ct == 1 ? 4 : 2; }
@@ -485,7 +508,7 @@ __global__ __launch_bounds__(64 * CT * bnb_groups(CT), 3) void k_ghead_bnb(
 //   G[q][co * 9 + r * 3 + s] = dt[q - (r - 1, s - 1)][co],  db[co] = sum_p dt[p][co],
 // with a = relu(bn(x)) recomputed from x and dt = dimg (1 - img^2): the
 // positions q are the K side of a (C x 32) product on the fp32 matrix cores.
-// A block takes ghead_wrows(W) rows of one image.  dt of those rows plus a
+// A block takes ghead_wrows rows of one image.  dt of those rows plus a
 // one-pixel zero frame is staged in LDS, so the 27 columns of G are plain
 // reads from it; each wave takes 16-position chunks of a, normalised once
 // into its LDS tile [position][channel] (the channel is the M side of the
@@ -496,14 +519,11 @@ constexpr size_t kWgLds = 64 * 1024;
 static size_t ghead_lds_at(int tr, int W, int Cp) {
   return ((size_t)(tr + 2) * (W + 2) * 3 + 3) / 4 * 16 + (size_t)4 * kWC * (Cp + 4) * 4 + 3 * (size_t)Cp * 4 + 768 * 4;
 }
-// rows per weight-gradient block: about 2048 positions, fewer while that leaves
-// less than 512 blocks (two per CU; 256 blocks: 79 us, 512: 58) or the LDS
-// tile does not fit
+// rows per weight-gradient block: 2048 positions at most
 static int ghead_wrows(int B, int H, int W, int Cp) {
-  int tr = std::max(1, std::min(16, 2048 / W));
-  tr = (int)std::max<int64_t>(1, std::min<int64_t>(tr, (int64_t)B * H / 512));
-  while (tr > 1 && ghead_lds_at(tr, W, Cp) > kWgLds) --tr;
-  return tr;
+  int most = std::max(1, std::min(16, 2048 / W));
+  while (most > 1 && ghead_lds_at(most, W, Cp) > kWgLds) --most;
+  return ghead_best_rows(B, H, most, 1.3);
 }
 
 bool ghead_shape_ok(int W, int C) {
@@ -692,6 +712,7 @@ void ghead_fwd(hipStream_t st, const void* x, int B, int H, int W, int C, int Cp
   const int64_t blocks = (int64_t)B * cdiv(H, TH) * cdiv(W, TC);
   PG_CHECK(blocks < (1LL << 31) && Cp == cpad(C) && ghead_shape_ok(W, C), "ghead_fwd: shape");
   const bf16_t* xb = (const bf16_t*)x;
+  ProfScope ps(st);
 #define PG_GHF(CK)                                                                                              \
   hipLaunchKernelGGL(k_ghead_fwd<CK>, dim3((unsigned)blocks), dim3(256), 0, st, xb, H, W, C, TC, TH, mean, scale, \
                      shift, Wt, sigma, bias, img)
@@ -703,6 +724,7 @@ void ghead_fwd(hipStream_t st, const void* x, int B, int H, int W, int C, int Cp
   }
 #undef PG_GHF
   PG_LAUNCH_CHECK();
+  ps.done("k_ghead_fwd<" + std::to_string(Cp) + "," + std::to_string(TH) + ">", 54.0 * B * H * W * C);
 }
 
 void ghead_wgrad(hipStream_t st, const float* dimg, int ldd, const float* img, const void* x, int B, int H, int W,
@@ -714,6 +736,7 @@ void ghead_wgrad(hipStream_t st, const float* dimg, int ldd, const float* img, c
   const int nch = (int)ghead_wgrad_blocks(B, H, W, Cp);
   const FastDiv fdW = make_fastdiv((uint32_t)W);
   const bf16_t* xb = (const bf16_t*)x;
+  ProfScope ps(st);
 #define PG_GHW(CT)                                                                                                   \
   hipLaunchKernelGGL(k_ghead_wgrad<CT>, dim3(nch), dim3(256), lds, st, dimg, ldd, img, xb, H, W, fdW, C, TRW, mean,  \
                      scale, shift, (float*)ws)
@@ -727,6 +750,7 @@ void ghead_wgrad(hipStream_t st, const float* dimg, int ldd, const float* img, c
   hipLaunchKernelGGL(k_ghead_fin, dim3((unsigned)cdiv(27 * C + 3, 64)), dim3(1024), 0, st, (const float*)ws, nch,
                      27 * C + 3, dwsn, dbias);
   PG_LAUNCH_CHECK();
+  ps.done("k_ghead_wgrad<" + std::to_string(Cp) + "," + std::to_string(TRW) + ">", 54.0 * B * H * W * C);
 }
 
 size_t ghead_bnb_ws_bytes(int B, int H, int W, int C) {
@@ -749,6 +773,7 @@ void ghead_bnb(hipStream_t st, const float* dimg, int ldd, const float* img, con
   const size_t lds = ghead_bnb_lds_at(TR, W, Cp);
   const FastDiv fdW = make_fastdiv((uint32_t)W), fdW2 = make_fastdiv((uint32_t)W + 2);
   const bf16_t* xb = (const bf16_t*)x;
+  ProfScope ps(st);
 #define PG_GHB(CT, AP)                                                                                            \
   hipLaunchKernelGGL((k_ghead_bnb<CT, AP>), dim3((unsigned)nb), dim3(64 * CT * bnb_groups(CT)), lds, st, dimg,    \
                      ldd, img, xb, H, W, fdW, fdW2, C, TR, Wt, sigma, mean, rstd, gain, bias, A, Bc, p1, p2,      \
@@ -766,6 +791,8 @@ void ghead_bnb(hipStream_t st, const float* dimg, int ldd, const float* img, con
 #undef PG_GHB4
 #undef PG_GHB
   PG_LAUNCH_CHECK();
+  // (both passes form the products)
+  ps.done("k_ghead_bnb<" + std::to_string(Cp) + "," + std::to_string(TR) + ">", 108.0 * B * H * W * C);
 }
 
 // --------------------------------------------------- discriminator head
