@@ -1,8 +1,10 @@
 """Parity of the launch forms that sizes decide: convolutions whose K
 loop is split over blocks, weight gradients planned in whole rounds of
-blocks, the conditional-BN linear maps and the sub-pixel fold.  Sizes at the edges of their tiles: partial pixel
-and channel tiles, uneven last splits, every gather and epilogue of a split
-conv.  Same oracle and bars as the block tests."""
+blocks, the conditional-BN linear maps, the sub-pixel fold and both fp32
+convolution kernels.  Sizes at the edges of their tiles: partial pixel and
+channel tiles, uneven last splits, every gather and epilogue of a split conv.
+Same oracle and bars as the block tests; where a case is there for a kernel,
+the kernels of its own run are checked by name."""
 import pytest
 
 from paragan_2411_03999_amd import lib
@@ -13,8 +15,14 @@ from .test_gpu_blocks import run_dblock, run_gblock
 pytestmark = pytest.mark.gpu
 
 
-def split_convs():
-    return {n for n in parity.SEEN if n.startswith("k_conv_") and n.endswith("/split")}
+def launched(kind, **shape):
+    """The named kernels that this run launched."""
+    before = set(parity.SEEN)
+    parity.SEEN.clear()
+    (run_gblock if kind == "g" else run_dblock)(weights="gaussian", **shape)
+    ran = set(parity.SEEN)
+    parity.SEEN.update(before)
+    return ran
 
 
 # (kind, shape, the split kernels that must have run, by family and gather)
@@ -33,26 +41,32 @@ SPLIT = [
 
 @pytest.mark.parametrize("kind,shape,parts", SPLIT)
 def test_split_conv(kind, shape, parts):
-    run = run_gblock if kind == "g" else run_dblock
-    before = split_convs()
-    parity.SEEN.difference_update(before)
-    run(dtype=lib.BF16, seed=700, weights="gaussian", **shape)
-    ran = split_convs()
-    parity.SEEN.update(before)
+    ran = {n for n in launched(kind, dtype=lib.BF16, seed=700, **shape) if n.endswith("/split")}
     for family, part in parts:
         assert any(n.startswith("k_conv_" + family) and part in n for n in ran), (family, part, sorted(ran))
 
 
-# Weight-gradient plans: row-tap tiles on a two-row image, a pixel range that
-# ends inside a stage and inside the last split, fewer pixels than one split
-@pytest.mark.parametrize("kind,shape", [
-    ("d", dict(B=1, H=2, W=32, cin=64, cout=256, preact=True, down=False, lsc=True)),
-    ("d", dict(B=2, H=33, W=31, cin=96, cout=192, preact=True, down=False, lsc=True)),
-    ("g", dict(B=1, H=3, W=3, cin=64, cout=384, dc=20)),
+# Weight-gradient plans.  Row-tap kernels (192 and 256 channels) on two-row
+# images: uneven last splits, a last split of one stage, 41 splits (the
+# reduction over waves); tiles of taps: one split, a pixel range that ends
+# inside a stage and inside the last split, fewer pixels than one split
+@pytest.mark.parametrize("kind,shape,names", [
+    ("d", dict(B=1, H=2, W=32, cin=256, cout=512, copies=152, preact=True, down=False, lsc=True),
+     ["k_wgrad_row3<256x192,false,true>"]),
+    ("d", dict(B=1, H=2, W=32, cin=192, cout=192, copies=257, preact=True, down=False, lsc=False),
+     ["k_wgrad_row3<192x192,false,true>"]),
+    ("d", dict(B=1, H=2, W=32, cin=128, cout=192, copies=384, preact=True, down=False, lsc=True),
+     ["k_wgrad_row3<192x192,false,true>"]),
+    ("d", dict(B=1, H=2, W=32, cin=64, cout=256, preact=True, down=False, lsc=True),
+     ["k_wgrad_tr<128x128,false,G_DIRECT,true>"]),
+    ("d", dict(B=2, H=33, W=31, cin=96, cout=192, preact=True, down=False, lsc=True),
+     ["k_wgrad_tr<128x128,false,G_DIRECT,true>"]),
+    ("g", dict(B=1, H=3, W=3, cin=64, cout=384, dc=20), ["SUB"]),
 ])
-def test_wgrad_plan(kind, shape):
-    run = run_gblock if kind == "g" else run_dblock
-    run(dtype=lib.BF16, seed=710, weights="gaussian", **shape)
+def test_wgrad_plan(kind, shape, names):
+    ran = launched(kind, dtype=lib.BF16, seed=710, **shape)
+    for name in names:
+        assert any(n.startswith("k_wgrad_") and name in n for n in ran), (name, sorted(ran))
 
 
 # Conditional-BN maps: conditioning wider than one staged chunk and not a
@@ -77,12 +91,12 @@ def test_cbn_maps(shape, dtype):
     (dict(B=2, H=128, W=128, cin=32, cout=96, copies=256), "k_wgrad_tr<96x384,false,G_S2,true>"),
 ])
 def test_network_instances(shape, name):
-    run_dblock(preact=True, down=True, lsc=True, dtype=lib.BF16, seed=730, weights="gaussian", **shape)
-    assert name in parity.SEEN
+    ran = launched("d", preact=True, down=True, lsc=True, dtype=lib.BF16, seed=730, **shape)
+    assert name in ran, sorted(ran)
 
 
-# fp32 convolutions in 32 x 32 tiles, the K steps over four waves: fewer steps
-# than waves (one 1x1 step), pixels past a tile, every gather and epilogue
+# fp32 convolutions with a wave per 16 x 16 tile: fewer K steps than loads in
+# flight (one 1x1 step), pixels past a tile, every gather and epilogue
 @pytest.mark.parametrize("kind,shape", [
     ("g", dict(B=1, H=3, W=3, cin=20, cout=36, dc=9)),
     ("g", dict(B=2, H=5, W=7, cin=72, cout=40, dc=9)),
@@ -90,5 +104,21 @@ def test_network_instances(shape, name):
     ("d", dict(B=2, H=5, W=3, cin=40, cout=40, preact=True, down=False, lsc=False)),
 ])
 def test_f32_small(kind, shape):
-    run = run_gblock if kind == "g" else run_dblock
-    run(dtype=lib.F32, seed=740, weights="gaussian", **shape)
+    ran = launched(kind, dtype=lib.F32, seed=740, **shape)
+    assert any(n.startswith("k_conv_f32r") for n in ran) and not any(n.startswith("k_conv_f32mfma") for n in ran)
+
+
+# and in 64 x 64 tiles through LDS, from 384 tiles on: the same gathers
+# (direct, upsampled, 2x2-pooled operand) and the pooled output.  (G: images of
+# 15 x 17, since the gradients of the conditional maps add the batch's samples
+# one after another in fp32, up to B 2^-24 of the terms' magnitudes: 6e-6 at 97
+# images, 9e-5 -- against the bar of 1e-4 -- at the 1537 that 4 x 4 would take)
+@pytest.mark.parametrize("kind,shape,parts", [
+    ("g", dict(B=1, H=15, W=17, cin=20, cout=36, dc=9, copies=97), ["<0,0,0>", "<1,0,0>", "<2,0,0>"]),
+    ("d", dict(B=1, H=6, W=10, cin=20, cout=68, copies=1640, preact=True, down=True, lsc=True), ["<0,0,0>", "<0,0,1>"]),
+])
+def test_f32_large(kind, shape, parts):
+    ran = launched(kind, dtype=lib.F32, seed=741, **shape)
+    assert not any(n.startswith("k_conv_f32r") for n in ran)
+    for part in parts:
+        assert "k_conv_f32mfma" + part in ran, (part, sorted(ran))
