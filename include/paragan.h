@@ -40,6 +40,13 @@
  *   normalisation keeps one persistent fp32 vector u (length = the weight's
  *   row count, Cout) per SN weight in a separate flat "u" buffer, in
  *   layout order; training-mode forwards update it in place.
+ * - Repeatability: the same call on the same values gives the same bits.
+ *   Between calls of other sizes an image's last bits may differ, also where
+ *   nothing couples the batch (the discriminator): kernels, and for the
+ *   single-block calls the number of partial sums of a convolution, follow
+ *   the batch.  A block called on its own and the same block inside a
+ *   network may differ in the same way.  fp32 convolutions sum in one order
+ *   at every size.
  * - Threading: a context is used by one host thread at a time.
  */
 #ifndef PARAGAN_H

@@ -110,9 +110,11 @@ PG_DEV void load8(const void* p, bool f32, int i, float* v) {
 // swizzled element offset of (row r, 16-byte chunk c) in a tile of 32-element rows
 PG_DEV int sw_off(int r, int c) { return r * 32 + 8 * (c ^ ((r >> 2) & 3)); }
 
-// One K step of a wave (KS channels): operand fragments of one LDS stage
-// through the MFMAs, KS / 16 of them per output tile.
-template <int TN, int TM, bool RELU, int KS>
+constexpr int KS = 32;   // channels per K step: 64-byte LDS rows
+
+// One K step of a wave: operand fragments of one LDS stage through the
+// MFMAs, KS / 16 of them per output tile.
+template <int TN, int TM, bool RELU>
 PG_DEV void conv_step(const bf16_t* xs, const bf16_t* ws, int xbase, int wbase, const int (&rdo)[KS / 16],
                       f32x16 (&acc)[TN][TM]) {
 #pragma unroll
@@ -277,12 +279,11 @@ PG_DEV void conv_epilogue(const CfK& k, f32x16 (&acc)[TN][TM], bf16_t* lds, int 
   }
 }
 
-template <int WN, int WM, int TN, int TM, int NS, int KS, int GATHER, bool RELU>
+template <int WN, int WM, int TN, int TM, int NS, int GATHER, bool RELU>
 __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k) {
   constexpr int NW = WN * WM;                  // waves per block (4 or 8)
   constexpr int NT = NW * 64;
   constexpr int BN = WN * TN * 32, BM = WM * TM * 32;
-  static_assert(KS == 32 || KS == 64, "channels per step");
   constexpr int CH = KS / 8;                   // 16-byte chunks per LDS row
   constexpr int RPL = 64 / CH;                 // rows filled by one wave load (1 KB)
   constexpr int RG = RPL * NW;                 // tile rows covered by one load of every wave
@@ -314,14 +315,10 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k)
 
   // Load j of this wave covers tile rows RPL (NW j + wave) .. + RPL - 1;
   // lane l fills row + l / CH, LDS chunk l % CH, which in the swizzled
-  // layout holds source chunk (l % CH) ^ swz(row): rows of 64 bytes swizzle
-  // by (row / 4) % 4, rows of 128 bytes by (row / 2) % 8 (bits of the row
-  // that a load's base, a multiple of RPL, leaves alone apart from bit 3,
-  // whose value -- the parity of NW j + wave -- is that of wave).
+  // layout holds source chunk (l % CH) ^ ((row / 4) % 4) (bits of the row
+  // that a load's base, a multiple of RPL = 16, leaves alone).
   const int lrow = lane / CH;
-  const int lrow_all = RPL * wave + lrow;      // row of load 0 (same swizzle for every load)
-  const uint32_t lchunk =
-      (uint32_t)((lane % CH) ^ (KS == 32 ? ((lrow_all >> 2) & 3) : ((lrow_all >> 1) & 7)));
+  const uint32_t lchunk = (uint32_t)((lane % CH) ^ ((lrow >> 2) & 3));
   int rb[AP], roh[AP], row_[AP];
   bool rv[AP];
 #pragma unroll
@@ -389,7 +386,7 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k)
 
   // operand read offsets: row (tile base + lane%32), chunk 2*kk + lane/32
   const int lr = lane & 31, h = lane >> 5;
-  const int f = KS == 32 ? ((lr >> 2) & 3) : ((lr >> 1) & 7);
+  const int f = (lr >> 2) & 3;
   int rdo[KS / 16];
 #pragma unroll
   for (int kk = 0; kk < KS / 16; ++kk) rdo[kk] = lr * KS + 8 * ((2 * kk + h) ^ f);
@@ -420,7 +417,7 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k)
     for (int s = 0; s < NS; ++s) {
       wait_barrier<vm_cap((NS - 2) * LPS)>();
       issue((s + NS - 1) % NS);
-      conv_step<TN, TM, RELU, KS>(Xs[s], Ws[s], xbase, wbase, rdo, acc);
+      conv_step<TN, TM, RELU>(Xs[s], Ws[s], xbase, wbase, rdo, acc);
     }
   }
   // drain: at most 2 NS - 2 steps, the last NS - 1 of them issuing nothing
@@ -428,7 +425,7 @@ __global__ __launch_bounds__(WN * WM * 64, 8 / (WN * WM)) void k_conv_fwd(CfK k)
     const int st = ks % NS;
     wait_barrier_steps<LPS>(min(NS - 2, ksteps - 1 - ks));
     if (ks + NS - 1 < ksteps) issue((st + NS - 1) % NS);
-    conv_step<TN, TM, RELU, KS>(Xs[st], Ws[st], xbase, wbase, rdo, acc);
+    conv_step<TN, TM, RELU>(Xs[st], Ws[st], xbase, wbase, rdo, acc);
   }
 
   conv_epilogue<WN, WM, TN, TM, GATHER>(k, acc, lds, m0, n0, wn, wm, wave, lane, pa, pb, blk.split);
@@ -746,7 +743,7 @@ std::string launch_cfg(hipStream_t s, CfK& k, int gather, bool relu) {
   dim3 grid(k.tiles_m * k.tiles_n * (gather == G_SUB ? 4 : 1) * k.splits), block(64 * WN * WM);
 #define PG_CF_CASE(G, R_)                                                             \
   if (gather == G && relu == R_) {                                                    \
-    hipLaunchKernelGGL((k_conv_fwd<WN, WM, TN, TM, NS, 32, G, R_>), grid, block, 0, s, k); \
+    hipLaunchKernelGGL((k_conv_fwd<WN, WM, TN, TM, NS, G, R_>), grid, block, 0, s, k); \
     return "k_conv_fwd<" + std::to_string(BN) + "x" + std::to_string(BM) + "," #G "," #R_ ">"; \
   }
   PG_CF_CASE(G_DIRECT, false)
@@ -770,7 +767,6 @@ struct CfPlan {
 
 // bytes of one split's partials
 int64_t split_bytes(int gather, int64_t M, int Np) { return 4 * M * (gather == G_SUB ? 4 : 1) * Np; }
-
 
 // The tiles, with the measured time (us) of one 32-channel K step of a block
 // -- c1 with one block on its CU, c2 in a full round (two four-wave blocks
@@ -819,7 +815,7 @@ constexpr CfTile kCfTiles[] = {
 // (halo: chunks outside taps; ring: taps outside channels), by halo_family's
 // rule and not by the model; every tile of a family sums alike, so the model
 // picks among them.
-constexpr int kCUs = 256, kSplitSteps = 8;
+constexpr int kCUs = 256, kSplitSteps = 8;   // (an MI355X's CUs, on which the tiles' times were taken)
 
 // Whether a conv that must keep its sums' order takes a halo kernel: where
 // 256 x 256 tiles come in whole rounds over the CUs (the last at least three

@@ -317,7 +317,7 @@ __global__ __launch_bounds__(256, 2) void k_ghead_fwd(const bf16_t* __restrict__
 // pass 1 (APPLY false) sums dz and dz * xhat per block of TR rows of an image,
 // pass 2 writes dx = rstd (gain dz - A - xhat Bc) from their totals.  da took
 // 4 bytes per value written once and read twice: at 32 x 128 x 128 x 96 the
-// three kernels 58 + 54 + 64 us, these 69 + 70.
+// three kernels 55 + 51 + 63 us, these 59 + 64.
 // The channels are the M side, the positions the N side of the product, with
 // the rows of the filter operand permuted so that a lane ends with 16
 // consecutive channels of one position (16-byte loads and stores of x and

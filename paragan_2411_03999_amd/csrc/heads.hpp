@@ -19,7 +19,7 @@ size_t ghead_ws_bytes(int B, int H, int W, int C);
 void ghead_fwd(hipStream_t st, const void* x, int B, int H, int W, int C, int Cp, const float* mean,
                const float* scale, const float* shift, const float* Wt, const float* sigma, const float* bias,
                float* img);
-// da: fp32 [B][H][W][Cp] gradient of relu(bn(x)); dwsn: [3][3][3][C] gradient of W/sigma
+// dwsn: [3][3][3][C] gradient of W / sigma; ws: ghead_ws_bytes
 void ghead_wgrad(hipStream_t st, const float* dimg, int ldd, const float* img, const void* x, int B, int H, int W,
                  int C, int Cp, const float* mean, const float* scale, const float* shift, float* dwsn, float* dbias,
                  void* ws);

@@ -1166,7 +1166,7 @@ __global__ void k_cbn_tables(const float* cond, int dc, const float* Wg, const f
 // The launch is latency-bound (a few MB): tiles are 16 samples x 32
 // channels, and a tile's whole operands -- up to 160 conditioning values a
 // row, BigGAN's 148 -- are staged at once, so a block waits for memory once
-// per 160 values (32 samples x 192 channels: 19 us in 32-deep steps, 6 so).
+// per 160 values (32 samples x 192 channels: 19 us in 32-deep steps, 5 so).
 constexpr int kCbnK = 160, kCbnB = 16, kCbnC = 32, kCbnS = kCbnK + 4;
 __global__ __launch_bounds__(256) void k_cbn_lin(int B, int C, int Cp, int dc, const float* cond, const float* Wg,
                                                  const float* Wb, const float* sg, const float* sb,

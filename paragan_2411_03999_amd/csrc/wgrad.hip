@@ -563,8 +563,8 @@ bool row3_shape(int R, int Cin, int Np) {
 // rounds is what pays, each further split costs its partial sums a write and
 // a read in the reduction, and a tile costs its padded work through the
 // number of tiles.  (Filling four blocks a CU, whatever the last round:
-// 192 x 192 tiles over 524288 x 384 x 1728, 1026 blocks, 772 us; 504 blocks,
-// 617 us.  1x1 filters on 32 blocks of 32 stages: 40 us, on 216: 20.)
+// 192 x 192 tiles over 524288 x 384 x 1728, 1026 blocks, 775 us; 504 blocks,
+// 623 us.  1x1 filters on 32 blocks of 32 stages: 40 us, on 216: 20.)
 // row3: the row-tap kernel is a candidate.  classes: parity classes of the
 // sub-pixel form, which share the launch.
 // one_order: the splits, which set the order of a result's sums, are
