@@ -16,7 +16,8 @@
 // from HBM straight into LDS (buffer loads with an LDS destination: lane l
 // of a wave writes 16 bytes at M0 + 16 l, no registers or LDS stores
 // involved) through a ring of three stages, so the loads of step k + 2 are
-// in flight while step k computes; one barrier per step.  LDS rows are 64
+// in flight while step k computes (six on the 64-channel tiles of launches
+// of few blocks); one barrier per step.  LDS rows are 64
 // bytes (32 bf16 of K) with the 16-byte chunks XOR-swizzled by row, which
 // keeps the MFMA operand reads free of bank conflicts; the swizzle is
 // realised by choosing which source chunk each lane loads.  A ReLU on the
