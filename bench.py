@@ -61,9 +61,12 @@ PEAK_HBM_GBS = 8000.0         # MI355X HBM3E (published)
 # reads 0.5 GiB for it: x2.0; WRITE_SIZE reads 1 GiB: x1.0).  Valid only for
 # the kernel source they were taken on (sha1 prefix of the file).
 TRAFFIC = {
-    "k_conv_halo<192x128,false>": {"fetch": 2.0 * 301623.0 * 1024, "write": 263315.0 * 1024,
+    "k_conv_halo<96x256,G_SUB,false>": {"fetch": 2.0 * 509072.0 * 1024, "write": 612540.0 * 1024,
+                                        "source": "paragan_2411_03999_amd/csrc/convfwd.hip",
+                                        "sha1": "35a67bb7a7a6"},
+    "k_conv_halo<192x128,false>": {"fetch": 2.0 * 300532.0 * 1024, "write": 263315.0 * 1024,
                                    "source": "paragan_2411_03999_amd/csrc/convfwd.hip",
-                                   "sha1": "2dcb2f927810"},
+                                   "sha1": "35a67bb7a7a6"},
 }
 
 
